@@ -223,39 +223,131 @@ moments_kernel(const double* mom, double count, double* mean_out, double* var_ou
   var_out[vb] = m2[idx * 2 + 1] / count;
 }
 
-// Autocorrelation of a recorded chain (Sec. 5.1, Eq. CORR_COEFF), one
-// workgroup per bin b of trace [t][nb]: with mean mu and variance var over the
-// t samples, acf[n][b] = sum_{i < t-n} (x_i - mu)(x_{i+n} - mu) / ((t - n) var)
-// for n <= max_lag, and nc[b] = the first n with acf < 0.1 (-1 if none).  All
-// sums run in a fixed order.
+// Autocorrelation of a recorded chain (Sec. 5.1, Eq. CORR_COEFF) of trace
+// [t][nb]: with mean mu and variance var over the t samples of a bin,
+// acf[n][b] = sum_{i < t-n} (x_i - mu)(x_{i+n} - mu) / ((t - n) var), n <=
+// max_lag.
+//
+// t nb (max_lag + 1) FP64 products against t nb samples: bound by the FP64
+// units once enough workgroups share the work, so a workgroup takes kAcfBins
+// neighbouring bins (64 B of every trace row) and kAcfLags lags and walks the
+// whole series in tiles of kAcfRows rows, the next tile's loads in flight
+// during the products of this one.  32 threads per bin each hold kAcfRun
+// consecutive rows and the kAcfRun + kAcfLags - 1 later rows their lags need:
+// 39 LDS reads for 128 products.  An LDS run of 16 is padded to 17, which puts
+// the 32 threads of a bin on different banks.  All sums run in a fixed order.
+// 8000 samples of 32 bins, 400 lags: 55.8 us a call; one workgroup per bin and
+// whole lags per thread, read from memory, took 2,320 us.  Tiles of 256 rows
+// take 99 us and loads under a condition 115 us: the series is walked tile by
+// tile, and each tile costs one load latency.
+constexpr int kAcfBins = 8, kAcfLags = 8, kAcfRun = 16, kAcfRows = 512;
+constexpr int kAcfPad = kAcfRows / kAcfRun * (kAcfRun + 1);   // padded rows of one bin
+static_assert(kWienerThreads == kAcfBins * (kAcfRows / kAcfRun), "one run of rows per thread");
+
 __global__ void __launch_bounds__(kWienerThreads)
-acf_kernel(const double* trace, int t, int nb, int max_lag, double* acf, int32_t* nc) {
+acf_kernel(const double* trace, int t, int nb, int max_lag, int64_t items, double* acf) {
+  constexpr int ROWS_PER_LOAD = kWienerThreads / kAcfBins;   // 32
+  constexpr int LOADS = kAcfRows / ROWS_PER_LOAD;            // 16
+  constexpr int S = kAcfPad + kAcfRun + 1;                   // one more run of later rows
+  __shared__ double xa[kAcfBins * S], xw[kAcfBins * S];
   __shared__ double red[kWienerThreads];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  double x = 0.0;
-  for (int i = tid; i < t; i += kWienerThreads) x += trace[static_cast<size_t>(i) * nb + b];
-  const double mu = block_sum(red, x) / t;
-  __syncthreads();
-  x = 0.0;
-  for (int i = tid; i < t; i += kWienerThreads) {
-    const double dv = trace[static_cast<size_t>(i) * nb + b] - mu;
-    x += dv * dv;
-  }
-  const double var = block_sum(red, x) / t;
-  for (int n = tid; n <= max_lag; n += kWienerThreads) {
+  const int tid = threadIdx.x;
+  const int lrow = tid / kAcfBins, lbin = tid % kAcfBins;    // this thread's loads
+  const int cbin = tid / ROWS_PER_LOAD, run = tid % ROWS_PER_LOAD;   // this thread's products
+  const int groups = (nb + kAcfBins - 1) / kAcfBins;
+  // item = (lags, bins), bins fastest: neighbours share the trace's cache lines
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
+    const int b0 = static_cast<int>(item % groups) * kAcfBins;
+    const int n0 = static_cast<int>(item / groups) * kAcfLags;
+    const double* col = trace + min(b0 + lbin, nb - 1);   // a bin past the last is never written
+    // Rows past the end are loaded as the last row and replaced by 0 where they
+    // are used: loads under a condition would be waited for one by one.
+    auto row_at = [&](int64_t i) { return col[static_cast<size_t>(min(i, static_cast<int64_t>(t) - 1)) * nb]; };
+    // mean of every bin: 32 strided sums, added in order
     double sum = 0.0;
-    for (int i = 0; i + n < t; ++i)
-      sum += (trace[static_cast<size_t>(i) * nb + b] - mu) *
-             (trace[static_cast<size_t>(i + n) * nb + b] - mu);
-    acf[static_cast<size_t>(n) * nb + b] = sum / ((t - n) * var);
+    for (int64_t i0 = 0; i0 < t; i0 += 32 * ROWS_PER_LOAD) {
+      double x[32];
+#pragma unroll
+      for (int k = 0; k < 32; ++k) x[k] = row_at(i0 + lrow + k * ROWS_PER_LOAD);
+#pragma unroll
+      for (int k = 0; k < 32; ++k) sum += i0 + lrow + k * ROWS_PER_LOAD < t ? x[k] : 0.0;
+    }
+    red[tid] = sum;
+    __syncthreads();
+    double mu = 0.0;
+    for (int r = 0; r < ROWS_PER_LOAD; ++r) mu += red[r * kAcfBins + lbin];
+    mu /= t;
+    auto slot = [](int row) { return row + row / kAcfRun; };
+    double acc[kAcfLags] = {0.0}, sq = 0.0;
+    double pa[LOADS], pw[LOADS + 1];
+    auto fetch = [&](int64_t i0) {
+#pragma unroll
+      for (int k = 0; k < LOADS; ++k) {
+        const int64_t i = i0 + lrow + k * ROWS_PER_LOAD;
+        pa[k] = row_at(i);
+        pw[k] = row_at(i + n0);
+      }
+      pw[LOADS] = row_at(i0 + n0 + kAcfRows + lrow);
+    };
+    fetch(0);
+    for (int64_t i0 = 0; i0 < t; i0 += kAcfRows) {
+      __syncthreads();   // the previous tile is used up
+#pragma unroll
+      for (int k = 0; k < LOADS; ++k) {
+        const int64_t i = i0 + lrow + k * ROWS_PER_LOAD;
+        xa[lbin * S + slot(lrow + k * ROWS_PER_LOAD)] = i < t ? pa[k] - mu : 0.0;
+        xw[lbin * S + slot(lrow + k * ROWS_PER_LOAD)] = i + n0 < t ? pw[k] - mu : 0.0;
+      }
+      if (lrow < kAcfRun)
+        xw[lbin * S + slot(kAcfRows + lrow)] = i0 + n0 + kAcfRows + lrow < t ? pw[LOADS] - mu : 0.0;
+      __syncthreads();
+      if (i0 + kAcfRows < t) fetch(i0 + kAcfRows);
+      double x[kAcfRun], w[kAcfRun + kAcfLags - 1];
+#pragma unroll
+      for (int r = 0; r < kAcfRun; ++r) x[r] = xa[cbin * S + run * (kAcfRun + 1) + r];
+#pragma unroll
+      for (int r = 0; r < kAcfRun + kAcfLags - 1; ++r)
+        w[r] = xw[cbin * S + run * (kAcfRun + 1) + r + r / kAcfRun];
+#pragma unroll
+      for (int r = 0; r < kAcfRun; ++r) {
+        sq += x[r] * x[r];
+#pragma unroll
+        for (int j = 0; j < kAcfLags; ++j) acc[j] += x[r] * w[r + j];
+      }
+    }
+    // the 32 threads of a bin are one half of a wave
+#pragma unroll
+    for (int h = ROWS_PER_LOAD / 2; h > 0; h >>= 1) {
+      sq += __shfl_xor(sq, h);
+#pragma unroll
+      for (int j = 0; j < kAcfLags; ++j) acc[j] += __shfl_xor(acc[j], h);
+    }
+    if (run == 0 && b0 + cbin < nb) {
+      const double var = sq / t;
+#pragma unroll
+      for (int j = 0; j < kAcfLags; ++j) {
+        const int n = n0 + j;
+        if (n <= max_lag)
+          acf[static_cast<size_t>(n) * nb + b0 + cbin] = acc[j] / ((t - n) * var);
+      }
+    }
   }
-  __syncthreads();
-  if (tid == 0) {
-    int first = -1;
-    for (int n = 0; n <= max_lag && first < 0; ++n)
-      if (acf[static_cast<size_t>(n) * nb + b] < 0.1) first = n;
-    nc[b] = first;
+}
+
+// nc[b] = the first lag with acf < 0.1, -1 if none: one wave per bin.
+__global__ void __launch_bounds__(64)
+acf_length_kernel(const double* acf, int nb, int max_lag, int32_t* nc) {
+  const int b = blockIdx.x, lane = threadIdx.x;
+  for (int n0 = 0; n0 <= max_lag; n0 += 64) {
+    const int n = n0 + lane;
+    const bool low = n <= max_lag && acf[static_cast<size_t>(n) * nb + b] < 0.1;
+    const unsigned long long m = __ballot(low);
+    if (m != 0) {
+      if (lane == 0) nc[b] = n0 + __ffsll(m) - 1;
+      return;
+    }
   }
+  if (lane == 0) nc[b] = -1;
 }
 
 }  // namespace mf

@@ -76,6 +76,27 @@ def test_acf_kernel_matches_oracle():
     assert np.array_equal(nc.cpu().numpy(), nc_ref)
 
 
+@pytest.mark.parametrize("t,nb,lag", [(2, 1, 1), (3, 9, 2), (511, 3, 510), (512, 8, 8), (513, 17, 7),
+                                      (600, 8, 16), (1200, 33, 511)])
+def test_acf_at_tile_edges(t, nb, lag):
+    """Series lengths, bin counts and lags around the kernel's tiles of 512
+    rows, 8 bins and 8 lags; a constant series gives NaN and no length."""
+    import torch
+    rng = np.random.default_rng(100 * t + nb)
+    x = 5.0 + np.cumsum(rng.standard_normal((t, nb)), axis=0)
+    if nb > 1:
+        x[:, 1] = 3.0
+    c, nc = binding.acf(torch.from_numpy(x).cuda(), lag)
+    with np.errstate(invalid="ignore", divide="ignore"):
+        c_ref, nc_ref = diagnostics.acf_bins(x, lag)
+    c, nc = c.cpu().numpy(), nc.cpu().numpy()
+    assert np.array_equal(np.isnan(c), np.isnan(c_ref)) and np.array_equal(nc, nc_ref)
+    # sums of t products relative to t var: rounding below t 2^-53 t/(t - n),
+    # on a mean whose offset of 5 to 50 sigma costs another factor of it
+    tol = 100 * t * 2.0 ** -53 * t / (t - np.arange(lag + 1))[:, None]
+    assert np.all(np.abs(c - c_ref)[~np.isnan(c_ref)] <= np.broadcast_to(tol, c.shape)[~np.isnan(c_ref)])
+
+
 def test_graph_replays_record_too():
     w = workloads.small_workload(32, 8, precision="fp32", seed=71, rng_seed=72)
     pb = workloads.make_problem(w)
