@@ -143,7 +143,9 @@ mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
  * min(n_kernels, MF_NUM_KERNELS) sweep kernels to kernel_ms (host).  Sweep i
  * brackets only its kernel i mod MF_NUM_KERNELS, with events that skip the
  * system-scope fence, so every kernel is timed on n_sweeps / MF_NUM_KERNELS
- * sweeps (NaN for a kernel never timed: n_sweeps < MF_NUM_KERNELS). */
+ * sweeps (NaN for a kernel never timed: n_sweeps < MF_NUM_KERNELS).  Where
+ * mf_gibbs_sweep joins kernels (mf_set_tuning, the two-pass sweep), this call
+ * runs their parts one by one, with the same results to the last bit. */
 mf_status mf_gibbs_sweep_timed(mf_problem* p, int32_t n_sweeps, void* stream,
                                double* kernel_ms, int32_t n_kernels);
 
@@ -220,7 +222,13 @@ mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
  * Path 0 (split, 32 <= N <= 256): the y-passes also run the radix-N/16 half
  * of the x-DFT, and the x-pass runs 16-point DFTs in registers.
  * Path 1 (whole): the x-pass runs whole x pencils through LDS.  It is the
- * only path for N = 8, 16, 512.
+ * only path for N = 8, 16, 512.  Up to N = 128 a run of n whole-path sweeps
+ * joins the y-passes between its x-passes with the z-pass (a (kz, iy) plane
+ * fits the LDS of a CU): 2 n + 1 launches.  The split path with its three
+ * choices at their defaults stands for the library's faster one there, which
+ * up to N = 128 is the same two-pass sweep (except FP64 problems of 96^3 and
+ * 128^3 with more than 256 planes of constant ix); other choices run the split
+ * path itself.
  * On the split path three choices are open:
  *  - x_tile: the x-pass workgroup (variant 0 is the library's tile rule,
  *    e.g. 128 iy columns x 2 k1 values at 256, with 8 LDS shell histograms
@@ -236,8 +244,8 @@ mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
  * grouped by workgroup, the transforms factor differently) and leaves the
  * same state between sweeps, so choices may change at any time.  The
  * default is the split path where it exists, x tile 0 (1 above 255 bins),
- * y group 0 and y_radix 0.  Mixing sweeps and the Wiener filter always use
- * the split path with x tile 1.
+ * y group 0 and y_radix 0.  Mixing sweeps always use the split path with x
+ * tile 1; the Wiener filter uses the default's schedule.
  * mf_set_x_path: MF_E_UNSUPPORTED_SIZE for the split path outside 32..256.
  * mf_set_tuning / mf_get_tuning: the path and the three choices at once;
  *   mf_get_tuning also fills the geometry they stand for.  MF_E_INVALID_ARG
@@ -280,7 +288,7 @@ mf_status mf_autotune(mf_problem* p, int32_t trials, void* stream, double* ms, m
 /* Algorithmic HBM bytes of one sweep, per kernel (bytes[MF_NUM_KERNELS], in
  * sweep order), summed over the problem's chains.  Each pass reads and
  * writes the half-complex field once, 2 (N/2 + 1) N^2 reals each way.  On
- * top of that:
+ * top of that (on the two-pass sweep the y-passes move nothing of their own):
  *  - the z-pass reads the two messenger coefficients of every voxel in the
  *    chunks of its tiles that hold an observed voxel (a chunk is one element
  *    of every lane of a tile; chunks with none skip the read);

@@ -26,6 +26,13 @@
 
 #include <hip/hip_runtime.h>
 
+// Multiplications and additions fuse within an expression only, as written: a
+// product fused across statements depends on what the optimizer sees around it,
+// and the kernels that compute one thing in several instantiations (the plane
+// kernel's joined and separate launches, its two workgroup sizes) have to agree
+// to the last bit.
+#pragma clang fp contract(on)
+
 namespace mf {
 
 template <typename R>

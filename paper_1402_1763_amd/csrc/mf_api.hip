@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "mf.h"
+#include "plane_kernels.hpp"
 #include "stream_kernels.hpp"
 #include "sweep_kernels.hpp"
 #include "wiener_kernels.hpp"
@@ -53,11 +54,15 @@ bool supported(int n) {
          n == 256 || n == 512;
 }
 
-// The two ways of running the x transform.  kPathSplit (32 <= N <= 256):
-// the y-passes carry its radix-N/16 half, and the x-pass runs 16-point DFTs
-// in registers.  kPathWhole: the x-pass runs whole x pencils through LDS.
-// Both leave the same state between sweeps, so a problem may switch.
-enum XPath : int { kPathSplit = 0, kPathWhole = 1 };
+// The ways of running the x transform.  kPathSplit (32 <= N <= 256): the
+// y-passes carry its radix-N/16 half, and the x-pass runs 16-point DFTs in
+// registers.  kPathWhole: whole x pencils through LDS.  kPathPlane (N <= 128):
+// whole x pencils, with the z and y transforms of a plane in one kernel
+// (plane_kernels.hpp); not a caller's choice but what the whole path, and the
+// split path with the default tiles, run where it exists.  All leave the same
+// state between sweeps, so a problem may switch.
+enum XPath : int { kPathSplit = 0, kPathWhole = 1, kPathPlane = 2 };
+constexpr int kMaxPlaneN = 128;
 
 // Tile variants of the split path searched by the autotuner: x-pass tiles
 // (XSTile<R, N, V>) and y-pass workgroup sizes (YSTile<R, N, V>).
@@ -68,7 +73,7 @@ struct Geometry {
   template <int V>
   static constexpr int split_wpp() {
     if constexpr (mf::split_x<N>()) return mf::XSTile<R, N, V>::WPP;
-    else return N / mf::XTile<R, N>::P;
+    else return whole_wpp();
   }
   template <int V>
   static constexpr int y_units() {
@@ -102,7 +107,11 @@ struct Geometry {
     if constexpr (mf::split_x<N>()) return mf::XSTile<R, N, V>::MAX_BINS;
     else return 0;
   }
-  static constexpr int xp_whole = N / mf::XTile<R, N>::P;
+  static constexpr int whole_wpp() {
+    if constexpr (mf::has_planes<N>()) return N / mf::ColTile<R, N>::P;
+    else return N / mf::XTile<R, N>::P;
+  }
+  static constexpr int xp_whole = whole_wpp();
   static constexpr int ztiles = (N / mf::ZTile<R, N>::IXB) * (N / mf::ZTile<R, N>::P);
   static constexpr int zept = mf::ZTile<R, N>::EPT;
 };
@@ -115,7 +124,7 @@ struct Shape {
   int x_max_bins[kTileVariants]; // most bins whose histograms fit the variant's LDS
   int y_units[kTileVariants];    // (kz, q) units per split y-pass workgroup, per variant
   int y_rev_distinct;            // the y radix schedule differs from its reverse
-  int xp_whole;                  // whole-pencil x-pass workgroups per kz plane
+  int xp_whole;                  // whole-pencil x-pass (column) workgroups per kz plane
   int ztiles;                    // z-pass tiles per chain
   int zept;                      // elements per z-pass lane (observation bits per tile)
 };
@@ -143,7 +152,7 @@ Shape shape_of(int n) {
 }
 
 struct Layout {
-  size_t ctr, tw, qthr, counts, tau, pk, table, status, partials, ratio, tobs, coef, omw, spec,
+  size_t ctr, tw, qthr, counts, tau, pk, table, status, partials, ratio, gam, tobs, coef, omw, spec,
       staging, rinv, total;
   size_t spec_elems, spec_stride;
   int n_wg_split[kTileVariants];   // split x-pass workgroups (one shell partial each) per variant
@@ -181,6 +190,7 @@ Layout make_layout(const mf_chain_desc& d) {
   L.status = take(nc * 4);
   L.partials = take(2 * nc * static_cast<size_t>(L.n_wg_max) * nb * 8);   // two sets (mixing)
   L.ratio = take(nc * nb * 8);
+  L.gam = take(d.n <= kMaxPlaneN ? mf::kGammaSlots * nc * nb * 8 : 0);
   L.tobs = take(nc * static_cast<size_t>(sh.ztiles) * 4);
   L.coef = take(nc * 2 * m * rs);
   L.omw = take(nc * m * rs);      // tau R^2 / N = 1 - alpha per voxel (Wiener filter only)
@@ -292,6 +302,23 @@ struct mf_problem {
   int xvar = 0, yvar = 0;       // split-path tile variants of Gibbs sweeps (autotuner)
   int yrad = 0;                 // 1: the split y-passes run their radix stages reversed
   int graphs = 0;               // live graphs that captured this problem's sweep
+  // Where the plane path is the faster one, by the problem alone (not by the
+  // chains of a call), us per sweep against the split path: one FP64 chain of
+  // 16^3 14.5 : 39.8, 32^3 15.5 : 39.8, 80^3 33.1 : 53.7, 128^3 70.8 : 73.5; one
+  // FP32 chain of 64^3 12.8 : 25.4, 96^3 22.0 : 30.1, 128^3 30.1 : 41.8; 32 FP32
+  // chains of 64^3 47.8 : 67.8, 8 of 96^3 60.5 : 69.3, 8 of 128^3 100 : 119.  FP64
+  // planes of 96^3 and 128^3 fill a CU's LDS and registers by themselves, so
+  // queues of them do not overlap: 8 chains of 96^3 157 : 152, 4 of 128^3 170 : 165.
+  bool prefers_planes() const {
+    return desc.n <= kMaxPlaneN && !(fp64() && desc.n >= 96 && desc.n * desc.n_chains > 256);
+  }
+  // The Gibbs sweep runs the plane kernels: on the whole path, and where they
+  // are preferred on the split path with nothing chosen away from its defaults.
+  bool planes() const {
+    if (xpath == kPathWhole) return desc.n <= kMaxPlaneN;
+    return prefers_planes() && xvar == default_xvar() && yvar == 0 && yrad == 0;
+  }
+  int sweep_path() const { return planes() ? kPathPlane : xpath; }
   // x-pass workgroups of a path; the split path's with x-tile variant xv
   int n_wg(int path, int xv) const { return path == kPathSplit ? L.n_wg_split[xv] : L.n_wg_whole; }
   // the default split x tile: 8 histogram copies per wave where they fit
@@ -310,6 +337,7 @@ mf::SweepArgs<R> args_of(const mf_problem* p, int path = -1, int xv = -1) {
   mf::SweepArgs<R> a{};
   char* ws = p->ws;
   a.spec = reinterpret_cast<mf::cx<R>*>(ws + p->L.spec);
+  a.spec_in = a.spec;
   a.coef = reinterpret_cast<const R*>(ws + p->L.coef);
   a.tile_obs = reinterpret_cast<const uint32_t*>(ws + p->L.tobs);
   a.ztiles = p->sh.ztiles;
@@ -325,6 +353,8 @@ mf::SweepArgs<R> args_of(const mf_problem* p, int path = -1, int xv = -1) {
   a.tw = reinterpret_cast<const mf::cx<R>*>(ws + p->L.tw);
   a.status = reinterpret_cast<uint32_t*>(ws + p->L.status);
   a.ctr = reinterpret_cast<uint32_t*>(ws + p->L.ctr);
+  a.gam = reinterpret_cast<double*>(ws + p->L.gam);
+  a.gam_chains = p->desc.n_chains;
   a.spec_stride = p->L.spec_stride;
   a.m = static_cast<size_t>(p->desc.n) * p->desc.n * p->desc.n;
   a.nb = p->desc.n_bins;
@@ -351,8 +381,67 @@ mf::SweepArgs<R> args_of(const mf_problem* p, int path = -1, int xv = -1) {
 
 enum KernelId {
   kZ = 0, kYF = 1, kX = 2, kYI = 3, kZSet = 10, kZGet = 11, kTable = 12,
-  kZDetK = 13, kZAccK = 14, kXDetK = 15, kXAdjK = 16, kXMixK = 17, kMixPkK = 18, kXMixInvK = 19
+  kZDetK = 13, kZAccK = 14, kXDetK = 15, kXAdjK = 16, kXMixK = 17, kMixPkK = 18, kXMixInvK = 19,
+  // plane path: the plane kernel's first, middle and last launch of a run of
+  // sweeps, its parts one by one, the deterministic middle launch, the P(k)
+  // workgroups alone, and the column kernel's modes
+  kPlaneFirst = 20, kPlaneMid = 21, kPlaneLast = 22, kPlaneZ = 23, kPlaneYF = 24, kPlaneDet = 25,
+  kPlanePk = 26, kColumn = 27, kColumnDet = 28, kColumnAdj = 29, kPlaneMidFull = 30, kPlaneGamma = 31
 };
+
+// pk_only, gamma_only: just those workgroups.
+template <typename R, int N, bool YI, int ZMODE, bool YF, bool FULL = false, bool MANY = false>
+void launch_plane(mf::SweepArgs<R> a, int nch, hipStream_t st, bool pk_only = false,
+                  bool gamma_only = false) {
+  constexpr int NT = mf::PlaneTile<R, N, MANY>::NT;
+  a.gam_wgs = FULL && a.sample_pk ? (static_cast<int>(mf::kGammaAhead) * a.nb + NT - 1) / NT : 0;
+  const int grid = a.gam_wgs + (gamma_only ? 0 : (YI ? a.nb : 0) + (pk_only ? 0 : N));
+  if (grid > 0)
+    hipLaunchKernelGGL((mf::plane_kernel<R, N, YI, ZMODE, YF, FULL, MANY>), dim3(grid, 1, nch), dim3(NT), 0, st, a);
+}
+
+template <typename R, int N, int XM>
+void launch_column(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
+  using T = mf::ColTile<R, N>;
+  const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
+  const int copies = XM == mf::kXDet ? 0 : mf::column_hist_copies<R, N>(a.nb);
+  hipLaunchKernelGGL((mf::column_kernel<R, N, XM>), dim3(N / T::P, N / 2 + 1, nch), dim3(T::NT),
+                     copies * mf::hist_stride(a.nb) * sizeof(double) + tables, st, a);
+}
+
+// The launches that a run repeats, with the workgroup for the number of planes:
+// more than the 256 CUs take, or not.
+template <typename R, int N, int ZMODE>
+void launch_plane_mid(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
+  using Sch = mf::PlaneRadices<N, sizeof(R) == 8>;
+  if constexpr (Sch::nt != Sch::ntb) {
+    if (N * nch > 256) return launch_plane<R, N, true, ZMODE, true, false, true>(a, nch, st);
+  }
+  launch_plane<R, N, true, ZMODE, true>(a, nch, st);
+}
+
+// The plane path's kernels; false for an id of another path.
+template <typename R, int N>
+bool launch_plane_path(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
+  using mf::kNoZ;
+  using mf::kZDet;
+  using mf::kZSweep;
+  switch (id) {
+    case kPlaneFirst: launch_plane<R, N, false, kZSweep, true, true>(a, nch, st); return true;
+    case kPlaneMidFull: launch_plane<R, N, true, kZSweep, true, true>(a, nch, st); return true;
+    case kPlaneGamma: launch_plane<R, N, false, kZSweep, true, true>(a, nch, st, false, true); return true;
+    case kPlaneMid: launch_plane_mid<R, N, kZSweep>(a, nch, st); return true;
+    case kPlaneLast: launch_plane<R, N, true, kNoZ, false>(a, nch, st); return true;
+    case kPlaneZ: launch_plane<R, N, false, kZSweep, false, true>(a, nch, st); return true;
+    case kPlaneYF: launch_plane<R, N, false, kNoZ, true>(a, nch, st); return true;
+    case kPlaneDet: launch_plane_mid<R, N, kZDet>(a, nch, st); return true;
+    case kPlanePk: launch_plane<R, N, true, kNoZ, false>(a, nch, st, true); return true;
+    case kColumn: launch_column<R, N, mf::kXSample>(a, nch, st); return true;
+    case kColumnDet: launch_column<R, N, mf::kXDet>(a, nch, st); return true;
+    case kColumnAdj: launch_column<R, N, mf::kXAdj>(a, nch, st); return true;
+  }
+  return false;
+}
 
 // Split-path y-pass with units variant V and radix order RV.
 template <typename R, int N, bool INV, int V, bool RV>
@@ -393,13 +482,14 @@ template <typename R, int N>
 void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool whole, int xv,
               int yv) {
   using ZT = mf::ZTile<R, N>;
-  using YT = mf::YTile<R, N>;
-  using XT = mf::XTile<R, N>;
   using XS = mf::XSTile<R, N, 1>;   // the modes other than Gibbs sampling
   constexpr bool can_split = mf::split_x<N>();
   const bool split = can_split && !whole;
   const dim3 zgrid(N / ZT::P, N / ZT::IXB, nch), zgrid1(N / ZT::P, N / ZT::IXB, 1);
   const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
+  if constexpr (mf::has_planes<N>()) {
+    if (launch_plane_path<R, N>(id, a, nch, st)) return;
+  }
   switch (id) {
     case kZ:
       hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZSweep>), zgrid, dim3(ZT::NT), 0, st, a);
@@ -423,8 +513,11 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
           break;
         }
       }
-      hipLaunchKernelGGL((mf::ypass_kernel<R, N, false>), dim3((N / 2 + 1) * N / YT::NPEN, 1, nch),
-                         dim3(YT::NT), 0, st, a);
+      if constexpr (!mf::has_planes<N>()) {
+        using YT = mf::YTile<R, N>;
+        hipLaunchKernelGGL((mf::ypass_kernel<R, N, false>), dim3((N / 2 + 1) * N / YT::NPEN, 1, nch),
+                           dim3(YT::NT), 0, st, a);
+      }
       break;
     case kYI:
       if constexpr (can_split) {
@@ -433,8 +526,11 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
           break;
         }
       }
-      hipLaunchKernelGGL((mf::ypass_kernel<R, N, true>),
-                         dim3((N / 2 + 1) * N / YT::NPEN + a.nb, 1, nch), dim3(YT::NT), 0, st, a);
+      if constexpr (!mf::has_planes<N>()) {
+        using YT = mf::YTile<R, N>;
+        hipLaunchKernelGGL((mf::ypass_kernel<R, N, true>),
+                           dim3((N / 2 + 1) * N / YT::NPEN + a.nb, 1, nch), dim3(YT::NT), 0, st, a);
+      }
       break;
     case kXDetK:
       if constexpr (can_split)
@@ -468,8 +564,11 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
           break;
         }
       }
-      hipLaunchKernelGGL((mf::xpass_kernel<R, N>), dim3(N / XT::P, N / 2 + 1, nch), dim3(XT::NT),
-                         mf::hist_doubles(XT::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
+      if constexpr (!mf::has_planes<N>()) {
+        using XT = mf::XTile<R, N>;
+        hipLaunchKernelGGL((mf::xpass_kernel<R, N>), dim3(N / XT::P, N / 2 + 1, nch), dim3(XT::NT),
+                           mf::hist_doubles(XT::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
+      }
       break;
     case kTable:
       hipLaunchKernelGGL((mf::pk_table_kernel<R>), dim3((a.nb + 63) / 64, nch), dim3(64), 0, st, a);
@@ -495,7 +594,7 @@ void launch(int id, const mf::SweepArgs<R>& a, int n, int nch, hipStream_t st, b
 }
 
 // path < 0: the problem's Gibbs-sweep path and tile variants; a given path
-// (the mixing sweep's split path) runs x-tile variant 1.
+// (the mixing sweep's split path, the plane path) runs x-tile variant 1.
 mf_status launch_checked(mf_problem* p, int id, int staging_chain, hipStream_t st, int path = -1,
                          int pk_mode = mf::kPkDraw) {
   const int nch = p->desc.n_chains;
@@ -549,7 +648,42 @@ mf_status write_counter(mf_problem* p, uint64_t sweep, hipStream_t st) {
   return MF_OK;
 }
 
+// The sweep's four kernels one by one.  The plane path's, too, compute what its
+// joined kernels do, bit for bit.
 const int kSweepOrder[MF_NUM_KERNELS] = {kZ, kYF, kX, kYI};
+const int kPlaneOrder[MF_NUM_KERNELS] = {kPlaneZ, kPlaneYF, kColumn, kPlaneLast};
+
+mf_status launch_sweep_kernel(mf_problem* p, int k, hipStream_t st) {
+  return p->planes() ? launch_checked(p, kPlaneOrder[k], 0, st, kPathPlane)
+                     : launch_checked(p, kSweepOrder[k], 0, st);
+}
+
+// The parts of a run of n sweeps: the first sweep, every further one, the end.
+// The plane path's gamma variates last kGammaAhead sweeps, so every
+// kGammaAhead-th sweep computes the next ones (full).
+enum RunPart : int { kRunFirst, kRunNext, kRunNextFull, kRunEnd, kRunParts };
+
+// Part of the i-th sweep of a run, whose index is `sweep`: one with recorded
+// moments takes the full plane kernel, too.
+RunPart run_part(const mf_problem* p, int i, uint64_t sweep) {
+  if (i == 0) return kRunFirst;
+  const DiagRec& d = p->diag;
+  const bool record = d.mom != nullptr && sweep >= d.start && (sweep - d.start) % d.thin == 0;
+  return record || i % static_cast<int>(mf::kGammaAhead) == 0 ? kRunNextFull : kRunNext;
+}
+
+mf_status launch_run_part(mf_problem* p, RunPart part, hipStream_t st) {
+  mf_status r = MF_OK;
+  if (p->planes()) {
+    if (part == kRunEnd) return launch_checked(p, kPlaneLast, 0, st, kPathPlane);
+    const int plane = part == kRunFirst ? kPlaneFirst : (part == kRunNext ? kPlaneMid : kPlaneMidFull);
+    r = launch_checked(p, plane, 0, st, kPathPlane);
+    return r != MF_OK ? r : launch_checked(p, kColumn, 0, st, kPathPlane);
+  }
+  for (int k = 0; k < MF_NUM_KERNELS && part != kRunEnd && r == MF_OK; ++k)
+    r = launch_checked(p, kSweepOrder[k], 0, st);
+  return r;
+}
 
 // Host FP64 -> device R copy through a temporary host buffer.
 mf_status upload_real(mf_problem* p, void* dst, const double* src, size_t count, hipStream_t st) {
@@ -836,13 +970,11 @@ mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
   if (room != MF_OK) return room;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   for (int i = 0; i < n_sweeps; ++i) {
-    for (int k = 0; k < MF_NUM_KERNELS; ++k) {
-      const mf_status st = launch_checked(p, kSweepOrder[k], 0, hs);
-      if (st != MF_OK) return st;
-    }
+    const mf_status st = launch_run_part(p, run_part(p, i, p->sweep), hs);
+    if (st != MF_OK) return st;
     ++p->sweep;
   }
-  return MF_OK;
+  return n_sweeps > 0 ? launch_run_part(p, kRunEnd, hs) : MF_OK;
 }
 
 mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
@@ -916,7 +1048,7 @@ mf_status timed_sweeps(mf_problem* p, int32_t n_sweeps, hipStream_t hs, double* 
         if (!device_ok(hipGetLastError(), "eviction stream launch")) break;
       }
       if (k == timed && !device_ok(hipEventRecord(ev[2 * i], hs), "hipEventRecord")) break;
-      st = launch_checked(p, kSweepOrder[k], 0, hs);
+      st = launch_sweep_kernel(p, k, hs);
       if (st == MF_OK && k == timed) device_ok(hipEventRecord(ev[2 * i + 1], hs), "hipEventRecord");
     }
     if (st == MF_OK) ++p->sweep;
@@ -1260,14 +1392,15 @@ mf_status mf_sweep_bytes(const mf_problem* p, size_t* bytes) {
   if (!p || !bytes) return fail(MF_E_INVALID_ARG, "NULL argument");
   const size_t rs = p->fp64() ? 8 : 4, n = p->desc.n, m = n * n * n, nb = p->desc.n_bins;
   const size_t spec = (n / 2 + 1) * n * n * 2 * rs;
-  const size_t part = static_cast<size_t>(p->n_wg(p->xpath, p->xvar)) * nb * 8;
+  const size_t part = static_cast<size_t>(p->n_wg(p->sweep_path(), p->xvar)) * nb * 8;
+  const size_t y = p->planes() ? 0 : 2 * spec;   // the plane kernel's y transforms move nothing
   for (int k = 0; k < MF_NUM_KERNELS; ++k) bytes[k] = 0;
   for (int c = 0; c < p->desc.n_chains; ++c) {
     const size_t coef = 2 * m * rs * static_cast<size_t>(p->obs_chunks[c]) / (p->sh.ztiles * p->sh.zept);
     bytes[0] += 2 * spec + coef;
-    bytes[1] += 2 * spec;
+    bytes[1] += y;
     bytes[2] += 2 * spec + part;
-    bytes[3] += 2 * spec + part + nb * (16 + 2 * rs);
+    bytes[3] += y + part + nb * (16 + 2 * rs);
   }
   return MF_OK;
 }
@@ -1286,7 +1419,14 @@ mf_status mf_debug_run_kernel(mf_problem* p, int32_t kernel, uint64_t sweep, voi
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const mf_status st = write_counter(p, sweep, hs);
   if (st != MF_OK) return st;
-  return launch_checked(p, kSweepOrder[kernel], 0, hs);
+  // the split path shows its own four kernels, also where its sweeps run planes;
+  // a plane path's last kernel alone has no earlier one to compute its gammas
+  if (p->xpath == kPathWhole && p->planes() && kernel == MF_NUM_KERNELS - 1) {
+    const mf_status g = launch_checked(p, kPlaneGamma, 0, hs, kPathPlane);
+    if (g != MF_OK) return g;
+  }
+  return p->xpath == kPathSplit ? launch_checked(p, kSweepOrder[kernel], 0, hs)
+                                : launch_sweep_kernel(p, kernel, hs);
 }
 
 mf_status mf_debug_spectrum(mf_problem* p, int32_t chain, double* buf, int32_t to_device,
@@ -1309,14 +1449,18 @@ struct mf_graph {
   std::vector<mf_problem*> probs;
   std::vector<hipStream_t> side;
   std::vector<hipEvent_t> events;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
+  // one graph per part of a run (RunPart); without a plane path there is one
+  // graph for every sweep, the first, and no end
+  hipGraph_t graph[kRunParts] = {};
+  hipGraphExec_t exec[kRunParts] = {};
   bool counted = false;   // probs' graph counts include this graph
   ~mf_graph() {
     if (counted)
       for (auto* p : probs) --p->graphs;
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
+    for (auto e : exec)
+      if (e) (void)hipGraphExecDestroy(e);
+    for (auto g : graph)
+      if (g) (void)hipGraphDestroy(g);
     for (auto e : events) (void)hipEventDestroy(e);
     for (auto s : side) (void)hipStreamDestroy(s);
   }
@@ -1358,26 +1502,31 @@ mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, 
     return bail("hipStreamCreateWithFlags", e);
   g->side.push_back(cap);
   hs = cap;
-  if ((e = hipStreamBeginCapture(hs, hipStreamCaptureModeThreadLocal)) != hipSuccess)
-    return bail("hipStreamBeginCapture", e);
-  mf_status st = MF_OK;
-  (void)hipEventRecord(g->events[n], hs);             // fork point
-  for (int i = 0; i < n && st == MF_OK; ++i) {
-    hipStream_t s2 = g->side[i];
-    (void)hipStreamWaitEvent(s2, g->events[n], 0);
-    for (int k = 0; k < MF_NUM_KERNELS && st == MF_OK; ++k)
-      st = launch_checked(problems[i], kSweepOrder[k], 0, s2);
-    (void)hipEventRecord(g->events[i], s2);
-    (void)hipStreamWaitEvent(hs, g->events[i], 0);     // join
+  bool any_planes = false;
+  for (int i = 0; i < n; ++i) any_planes |= problems[i]->planes();
+  for (int part = kRunFirst; part <= kRunEnd; ++part) {
+    if (part != kRunFirst && !any_planes) break;
+    if ((e = hipStreamBeginCapture(hs, hipStreamCaptureModeThreadLocal)) != hipSuccess)
+      return bail("hipStreamBeginCapture", e);
+    mf_status st = MF_OK;
+    (void)hipEventRecord(g->events[n], hs);             // fork point
+    for (int i = 0; i < n && st == MF_OK; ++i) {
+      if (part == kRunEnd && !problems[i]->planes()) continue;
+      hipStream_t s2 = g->side[i];
+      (void)hipStreamWaitEvent(s2, g->events[n], 0);
+      st = launch_run_part(problems[i], static_cast<RunPart>(part), s2);
+      (void)hipEventRecord(g->events[i], s2);
+      (void)hipStreamWaitEvent(hs, g->events[i], 0);     // join
+    }
+    e = hipStreamEndCapture(hs, &g->graph[part]);
+    if (st != MF_OK) {
+      delete g;
+      return st;
+    }
+    if (e != hipSuccess) return bail("hipStreamEndCapture", e);
+    if ((e = hipGraphInstantiate(&g->exec[part], g->graph[part], nullptr, nullptr, 0)) != hipSuccess)
+      return bail("hipGraphInstantiate", e);
   }
-  e = hipStreamEndCapture(hs, &g->graph);
-  if (st != MF_OK) {
-    delete g;
-    return st;
-  }
-  if (e != hipSuccess) return bail("hipStreamEndCapture", e);
-  if ((e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0)) != hipSuccess)
-    return bail("hipGraphInstantiate", e);
   // the graph holds the diagnostic buffers' addresses as captured
   for (auto* p : g->probs) ++p->graphs;
   g->counted = true;
@@ -1393,7 +1542,13 @@ mf_status mf_graph_launch(mf_graph* g, int32_t n_sweeps, void* stream) {
     if (room != MF_OK) return room;
   }
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  for (int i = 0; i < n_sweeps; ++i) MF_HIP(hipGraphLaunch(g->exec, hs));
+  for (int i = 0; i < n_sweeps; ++i) {
+    int part = kRunFirst;
+    if (g->exec[kRunEnd])
+      for (auto* p : g->probs) part = std::max<int>(part, run_part(p, i, p->sweep + i));
+    MF_HIP(hipGraphLaunch(g->exec[part], hs));
+  }
+  if (n_sweeps > 0 && g->exec[kRunEnd]) MF_HIP(hipGraphLaunch(g->exec[kRunEnd], hs));
   for (auto* p : g->probs) p->sweep += static_cast<uint64_t>(n_sweeps);
   return MF_OK;
 }
@@ -1503,7 +1658,7 @@ const R* omw_of(const mf_problem* p, int c) {
 template <typename R>
 mf::SweepArgs<R> wiener_args(const mf_problem* p, int c0, const R* coef, R* table, double* pkg,
                              double* gacc) {
-  mf::SweepArgs<R> a = args_of<R>(p, kPathSplit, 1);
+  mf::SweepArgs<R> a = args_of<R>(p, p->prefers_planes() ? kPathPlane : kPathSplit, 1);
   a.coef = coef;
   a.table = table;
   a.pk = pkg;
@@ -1532,26 +1687,45 @@ mf_status check_launch(const char* what) {
   return MF_OK;
 }
 
-// One iteration s' = C (cs alpha s + cb beta) of every chain on `spec`.
-// Forward (adj = false): t^ goes to aux when aux is set.  Adjoint (adj =
-// true): the per-bin sums of Re(conj(t^) aux) are added to gacc, and s is
-// added to acc when set.
+// One iteration s' = C (cs alpha s + cb beta) of every chain, from the field
+// in src to the one in dst (which may be the same).  Forward (adj = false): t^
+// goes to aux when aux is set.  Adjoint (adj = true): the per-bin sums of
+// Re(conj(t^) aux) are added to gacc, and s is added to acc when set.
+// On the plane path a field lacks the inverse y transform until wiener_finish,
+// and the sums of an adjoint iteration are added by the next one on the same
+// field (open = true) or by wiener_finish.
 template <typename R>
-mf_status wiener_iter(mf_problem* p, mf::SweepArgs<R> a, int nc, mf::cx<R>* spec, mf::cx<R>* aux,
-                      bool adj, R cs, R cb, R* acc, hipStream_t st) {
-  a.spec = spec;
+mf_status wiener_iter(mf_problem* p, mf::SweepArgs<R> a, int nc, const mf::cx<R>* src, mf::cx<R>* dst,
+                      mf::cx<R>* aux, bool adj, R cs, R cb, R* acc, hipStream_t st, bool open = false) {
+  a.spec_in = src;
+  a.spec = dst;
   a.aux = aux;
   a.acc = acc;
   a.cs = cs;
   a.cb = cb;
-  a.pk_mode = adj ? mf::kPkGrad : mf::kPkNone;
-  const int ids[4] = {kZDetK, kYF, adj ? kXAdjK : kXDetK, kYI};
-  for (int id : ids) {
-    launch<R>(id, a, p->desc.n, nc, st);
+  const bool planes = p->prefers_planes();
+  a.pk_mode = (planes ? open : adj) ? mf::kPkGrad : mf::kPkNone;
+  const int split[4] = {kZDetK, kYF, adj ? kXAdjK : kXDetK, kYI};
+  const int plane[2] = {kPlaneDet, adj ? kColumnAdj : kColumnDet};
+  for (int k = 0; k < (planes ? 2 : 4); ++k) {
+    launch<R>(planes ? plane[k] : split[k], a, p->desc.n, nc, st);
     const mf_status r = check_launch("Wiener iteration");
     if (r != MF_OK) return r;
   }
   return MF_OK;
+}
+
+// Completes the field after its last iteration: transformed along z only, the
+// sums of an adjoint iteration (open) added.  sums_only leaves the field.
+template <typename R>
+mf_status wiener_finish(mf_problem* p, mf::SweepArgs<R> a, int nc, mf::cx<R>* spec, bool open,
+                        hipStream_t st, bool sums_only = false) {
+  if (!p->prefers_planes()) return MF_OK;
+  a.spec_in = spec;
+  a.spec = spec;
+  a.pk_mode = open ? mf::kPkGrad : mf::kPkNone;
+  launch<R>(sums_only ? kPlanePk : kPlaneLast, a, p->desc.n, nc, st);
+  return check_launch("Wiener iteration's end");
 }
 
 // y = x / R for chains c0 .. c0 + nc - 1 (y may be x).  A problem with a
@@ -1592,22 +1766,26 @@ mf_status wiener_forward(mf_problem* p, int c0, const double* d, const double* p
                        reinterpret_cast<R*>(g + W.table) + c * 2 * nb, p->tau[c0 + c], vcell,
                        static_cast<double>(m), nb);
   }
+  // s_k is a checkpoint for every k divisible by `every`: the iteration before
+  // leaves it in the checkpoint's place, and the one after reads it there
+  auto* fwd = reinterpret_cast<mf::cx<R>*>(g + W.fwd);
+  auto ckpt = [&](int j) { return reinterpret_cast<mf::cx<R>*>(g + W.ckpt + static_cast<size_t>(j) * specs); };
   hipLaunchKernelGGL((mf::fill_zero_kernel<R>), dim3(1024), dim3(256), 0, st,
-                     reinterpret_cast<R*>(g + W.fwd), specs / sizeof(R));
+                     reinterpret_cast<R*>(ckpt(0)), specs / sizeof(R));
   mf_status r = check_launch("Wiener set-up");
   if (r != MF_OK) return r;
-  auto* fwd = reinterpret_cast<mf::cx<R>*>(g + W.fwd);
+  const mf::cx<R>* src = ckpt(0);
   for (int k = 0; k < n_iter; ++k) {
-    if (k % every == 0)
-      MF_HIP(hipMemcpyAsync(g + W.ckpt + static_cast<size_t>(k / every) * specs, fwd, specs,
-                            hipMemcpyDeviceToDevice, st));
-    if ((r = wiener_iter<R>(p, a, nc, fwd, nullptr, false, R(1), R(1), nullptr, st)) != MF_OK)
+    auto* dst = (k + 1) % every == 0 && k + 1 < n_iter ? ckpt((k + 1) / every) : fwd;
+    if ((r = wiener_iter<R>(p, a, nc, src, dst, nullptr, false, R(1), R(1), nullptr, st)) != MF_OK)
       return r;
+    src = dst;
   }
+  if ((r = wiener_finish<R>(p, a, nc, fwd, false, st)) != MF_OK) return r;
   const R* s = reinterpret_cast<const R*>(p->ws + p->L.staging);
   for (int c = 0; c < nc; ++c) {   // s_K of chain c through the state staging buffer
     auto ag = a;
-    ag.spec = fwd;
+    ag.spec_in = fwd;
     ag.staging_chain = c;
     launch<R>(kZGet, ag, n, 1, st);
     with_n(n, [&](auto nn) {
@@ -1651,15 +1829,17 @@ mf_status wiener_backward(mf_problem* p, int c0, const double* d, char* g, const
   if (r != MF_OK) return r;
   for (int sg = W.n_ckpt - 1; sg >= 0; --sg) {
     const int k0 = sg * every, k1 = std::min(n_iter, k0 + every);
-    MF_HIP(hipMemcpyAsync(fwd, g + W.ckpt + static_cast<size_t>(sg) * specs, specs,
-                          hipMemcpyDeviceToDevice, st));
-    for (int k = k0; k < k1; ++k)
-      if ((r = wiener_iter<R>(p, a, nc, fwd, slot(k - k0), false, R(1), R(1), nullptr, st)) != MF_OK)
+    const auto* src = reinterpret_cast<const mf::cx<R>*>(g + W.ckpt + static_cast<size_t>(sg) * specs);
+    for (int k = k0; k < k1; ++k) {
+      if ((r = wiener_iter<R>(p, a, nc, src, fwd, slot(k - k0), false, R(1), R(1), nullptr, st)) != MF_OK)
         return r;
+      src = fwd;
+    }
+    if (sg == W.n_ckpt - 1 && (r = wiener_finish<R>(p, a, nc, fwd, false, st)) != MF_OK) return r;
     if (sg == W.n_ckpt - 1) {   // fwd holds s_K: the direct term w (2 d - s_K) of d chi2 / d d
       for (int c = 0; c < nc; ++c) {
         auto ag = a;
-        ag.spec = fwd;
+        ag.spec_in = fwd;
         ag.staging_chain = c;
         launch<R>(kZGet, ag, n, 1, st);
         with_n(n, [&](auto nn) {
@@ -1677,14 +1857,15 @@ mf_status wiener_backward(mf_problem* p, int c0, const double* d, char* g, const
       if (k == n_iter - 1) {
         auto af = a;
         af.cb_over_tau = 1;
-        r = wiener_iter<R>(p, af, nc, adj, slot(k - k0), true, R(0), R(-1), nullptr, st);
+        r = wiener_iter<R>(p, af, nc, adj, adj, slot(k - k0), true, R(0), R(-1), nullptr, st);
       } else {
-        r = wiener_iter<R>(p, a, nc, adj, slot(k - k0), true, R(1), R(0), acc, st);
+        r = wiener_iter<R>(p, a, nc, adj, adj, slot(k - k0), true, R(1), R(0), acc, st, true);
       }
       if (r != MF_OK) return r;
     }
   }
-  a.spec = adj;
+  if ((r = wiener_finish<R>(p, a, nc, adj, true, st)) != MF_OK) return r;
+  a.spec_in = adj;
   a.acc = acc;
   launch<R>(kZAccK, a, n, nc, st);   // adds r_0
   for (int c = 0; c < nc; ++c) {
@@ -1833,25 +2014,27 @@ mf_status logdet_run(mf_problem* p, int c0, const double* pk, int n_iter, int n_
                            a.key1, entries);
       });
     }
+    // s_{K-1} stays in prev: the iteration before the last leaves it there
+    auto* first = n_iter == 1 ? prev : fwd;
     hipLaunchKernelGGL((mf::fill_zero_kernel<R>), dim3(1024), dim3(256), 0, st,
-                       reinterpret_cast<R*>(fwd), L.specs / sizeof(R));
+                       reinterpret_cast<R*>(first), L.specs / sizeof(R));
     if ((r = check_launch("log-determinant probe")) != MF_OK) return r;
+    const mf::cx<R>* src = first;
     for (int k = 0; k < n_iter; ++k) {
-      if (k == n_iter - 1)
-        MF_HIP(hipMemcpyAsync(prev, fwd, L.specs, hipMemcpyDeviceToDevice, st));
-      if ((r = wiener_iter<R>(p, a, nc, fwd, nullptr, false, R(1), R(1), nullptr, st)) != MF_OK)
+      auto* dst = k == n_iter - 2 ? prev : fwd;
+      if ((r = wiener_iter<R>(p, a, nc, src, dst, nullptr, false, R(1), R(1), nullptr, st)) != MF_OK)
         return r;
+      src = dst;
     }
-    MF_HIP(hipMemcpyAsync(scr, fwd, L.specs, hipMemcpyDeviceToDevice, st));
-    if ((r = wiener_iter<R>(p, a, nc, scr, aux, false, R(0), R(1), nullptr, st)) != MF_OK) return r;
+    if ((r = wiener_iter<R>(p, a, nc, fwd, scr, aux, false, R(0), R(1), nullptr, st)) != MF_OK) return r;
     hipLaunchKernelGGL((mf::fill_zero_kernel<double>), dim3(1), dim3(256), 0, st, g1,
                        static_cast<size_t>(nc) * nb);
     hipLaunchKernelGGL((mf::fill_zero_kernel<double>), dim3(1), dim3(256), 0, st, g0,
                        static_cast<size_t>(nc) * nb);
-    MF_HIP(hipMemcpyAsync(scr, fwd, L.specs, hipMemcpyDeviceToDevice, st));
-    if ((r = wiener_iter<R>(p, a, nc, scr, aux, true, R(1), R(1), nullptr, st)) != MF_OK) return r;
-    MF_HIP(hipMemcpyAsync(scr, prev, L.specs, hipMemcpyDeviceToDevice, st));
-    if ((r = wiener_iter<R>(p, a0, nc, scr, aux, true, R(1), R(1), nullptr, st)) != MF_OK) return r;
+    if ((r = wiener_iter<R>(p, a, nc, fwd, scr, aux, true, R(1), R(1), nullptr, st)) != MF_OK) return r;
+    if ((r = wiener_finish<R>(p, a, nc, scr, true, st, true)) != MF_OK) return r;
+    if ((r = wiener_iter<R>(p, a0, nc, prev, scr, aux, true, R(1), R(1), nullptr, st)) != MF_OK) return r;
+    if ((r = wiener_finish<R>(p, a0, nc, scr, true, st, true)) != MF_OK) return r;
     for (int c = 0; c < nc; ++c)
       hipLaunchKernelGGL(mf::logdet_combine_kernel, dim3((nb + 63) / 64), dim3(64), 0, st,
                          g1 + c * nb, g0 + c * nb, pkg + c * nb, p->tau[c0 + c], vcell,

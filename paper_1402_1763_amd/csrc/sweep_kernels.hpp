@@ -38,6 +38,7 @@ namespace mf {
 template <typename R>
 struct SweepArgs {
   cx<R>* spec;            // chain c at spec + c * spec_stride
+  const cx<R>* spec_in;   // what the z-pass (or plane pass) reads, laid out as spec (mostly spec itself)
   const R* coef;          // chain c at coef + c * 2 m (z-pass thread order)
   const uint32_t* tile_obs;  // [chain][z tile] bit e: element e of the tile holds an observed voxel
   int32_t ztiles;         // z-pass tiles per chain
@@ -77,6 +78,11 @@ struct SweepArgs {
   int32_t diag_thin;
   int32_t trace_cap;
   double vcell;
+  // Plane path: the gamma variates of the P draws, computed some sweeps ahead
+  // (they do not depend on the field); sweep n's at slot n mod kGammaSlots.
+  double* gam;            // [kGammaSlots][chain][nb]
+  int32_t gam_chains;     // chains of the problem (slot stride / nb)
+  int32_t gam_wgs;        // workgroups per chain of this launch that compute kGammaAhead sweeps
   // InvGamma(prior_a, prior_b) prior on P_b, prior_b in grid units; (0, 0) is
   // Jeffreys' prior
   double prior_a, prior_b;
@@ -260,6 +266,7 @@ zpass_kernel(SweepArgs<R> a) {
   const int ix0 = blockIdx.y * T::IXB;
   const int c = (MODE == kZSweep || MODE == kZDet || MODE == kZAccum)
                     ? static_cast<int>(blockIdx.z) : a.staging_chain;
+  const cx<R>* src = a.spec_in + static_cast<size_t>(c) * a.spec_stride;
   cx<R>* spec = a.spec + static_cast<size_t>(c) * a.spec_stride;
   load_twiddles(tw, a.tw, N, NT);
   cx<R> v[EPT];
@@ -277,7 +284,7 @@ zpass_kernel(SweepArgs<R> a) {
       TL::template in_pos<false>(tid, e, pen, k);
       const int kk = k <= H ? k : N - k;
       cx<R> A, B;
-      ld2(spec + (static_cast<size_t>(kk) * N + ix0 + pen / NPAIR) * N + iy0 + 2 * (pen % NPAIR),
+      ld2(src + (static_cast<size_t>(kk) * N + ix0 + pen / NPAIR) * N + iy0 + 2 * (pen % NPAIR),
           A, B);
       if (k == 0 || k == H) v[e] = cx<R>{A.x, B.x};
       else if (k < H) v[e] = cx<R>{A.x - B.y, A.y + B.x};
@@ -446,7 +453,7 @@ __device__ __forceinline__ double sum_partials(const double* part, int n, double
   return red[0];
 }
 
-// P(k) step of bin b of chain c by one workgroup of NTH threads: sums the
+// P(k) step of sweep `sweep` for bin b of chain c by one workgroup of NTH threads: sums the
 // x-pass partials in a fixed order (sum_partials), forms
 // sigma_b = M^2 sum w |s^/M|^2 and draws P_b = (sigma_b + 2 M b0) / (2 M g),
 // g ~ Gamma(n_b / 2 + a0, 1) -- the inverse-gamma conditional of P_b under
@@ -454,8 +461,12 @@ __device__ __forceinline__ double sum_partials(const double* part, int n, double
 // (A_b, B_b).  With pk_mode == kPkGrad the workgroup instead adds
 // sum_wg partials / M to gacc[b] (the Wiener adjoint's d chi2 / d f_b);
 // kPkNone does nothing.
-template <typename R, int NTH>
-__device__ __forceinline__ void pk_draw_block(const SweepArgs<R>& a, int b, int c, double* red) {
+// STORED: the gamma variate comes from a.gam.
+constexpr uint32_t kGammaAhead = 32, kGammaSlots = 2 * kGammaAhead;
+
+template <typename R, int NTH, bool STORED = false>
+__device__ __forceinline__ void pk_draw_block(const SweepArgs<R>& a, int b, int c, double* red,
+                                              uint32_t sweep) {
   if (a.pk_mode == kPkNone) return;
   const int tid = threadIdx.x;
   sum_partials<NTH>(a.partials + (static_cast<size_t>(c) * a.nb + b) * a.n_wg_x, a.n_wg_x, red);
@@ -468,13 +479,17 @@ __device__ __forceinline__ void pk_draw_block(const SweepArgs<R>& a, int b, int 
     double* pk = a.pk + static_cast<size_t>(c) * a.nb;
     double p = pk[b];
     if (a.trace != nullptr) {
-      const int j = recorded(a, a.ctr[1]);
+      const int j = recorded(a, sweep);
       if (j >= 0 && j < a.trace_cap)
         a.trace[(static_cast<size_t>(c) * a.trace_cap + j) * a.nb + b] = p * a.vcell;
     }
     if (a.sample_pk && a.counts[b] > 0.0) {
-      const double g = gamma_mt(0.5 * a.counts[b] + a.prior_a, static_cast<uint32_t>(b), a.ctr[1],
-                                a.chain0 + c, a.key0, a.key1);
+      double g;
+      if (STORED)
+        g = a.gam[(static_cast<size_t>(sweep % kGammaSlots) * a.gam_chains + c) * a.nb + b];
+      else
+        g = gamma_mt(0.5 * a.counts[b] + a.prior_a, static_cast<uint32_t>(b), sweep, a.chain0 + c,
+                     a.key0, a.key1);
       p = (sigma + 2.0 * m * a.prior_b) / (2.0 * m * g);
       if (!(g > 0.0) || !isfinite(p) || !isfinite(sigma)) {
         atomicOr(a.status + c, 1u);
@@ -620,7 +635,7 @@ ypass_kernel(SweepArgs<R> a) {
   int blk = blockIdx.x;
   if (INV) {
     if (blk < a.nb) {
-      pk_draw_block<R, NT>(a, blk, blockIdx.z, reinterpret_cast<double*>(lds));
+      pk_draw_block<R, NT>(a, blk, blockIdx.z, reinterpret_cast<double*>(lds), a.ctr[1]);
       return;
     }
     blk -= a.nb;
@@ -698,7 +713,7 @@ ysplit_kernel(SweepArgs<R> a) {
   int blk = blockIdx.x;
   if (INV) {
     if (blk < a.nb) {
-      pk_draw_block<R, NT>(a, blk, blockIdx.z, reinterpret_cast<double*>(lds));
+      pk_draw_block<R, NT>(a, blk, blockIdx.z, reinterpret_cast<double*>(lds), a.ctr[1]);
       return;
     }
     blk -= a.nb;
@@ -836,7 +851,7 @@ __device__ __forceinline__ int k2_of(int e, int h0) {
 // w of the plane (1 on kz = 0, N/2, else 2) is applied per workgroup in
 // draw_epilogue.  This is the form for planes 0 < kz < N/2, where every
 // mode is drawn independently and q >= 1.
-template <typename R, int N, int RL, int S, bool MIX, int KS = 1>
+template <typename R, int N, int RL, int S, bool MIX, int KS = 1, bool XOR3 = false>
 __device__ __forceinline__ void draw_slot_plain(cx<R>* v, int q, int iy, int kz,
                                                 const SweepArgs<R>& a, const DrawCtx<R>& d,
                                                 int h0 = 0) {
@@ -849,7 +864,7 @@ __device__ __forceinline__ void draw_slot_plain(cx<R>* v, int q, int iy, int kz,
     R g[4];
     {
       const uint32_t w0 = static_cast<uint32_t>((kz * N + iy) * H + ixl);
-      const Words4 w = philox4x32_10(w0, d.sweep, kPhaseSignal, d.chain, a.key0, a.key1);
+      const Words4 w = philox4x32_10<XOR3>(w0, d.sweep, kPhaseSignal, d.chain, a.key0, a.key1);
       box_muller(w.x0, w.x1, g[0], g[1]);
       box_muller(w.x2, w.x3, g[2], g[3]);
     }
@@ -936,12 +951,12 @@ __device__ __forceinline__ void draw_slot_herm(cx<R>* v, int q, int iy, int kz,
 
 // MIX = true also adds Re(conj(s^/M) t^) to the second histogram (the
 // mixing sweep's cross term).
-template <typename R, int N, int RL, int S, bool MIX = false, int KS = 1>
+template <typename R, int N, int RL, int S, bool MIX = false, int KS = 1, bool XOR3 = false>
 __device__ __forceinline__ void draw_slot(cx<R>* v, int q, int iy, int kz,
                                           const SweepArgs<R>& a, const DrawCtx<R>& d,
                                           int h0 = 0) {
   if (kz == 0 || kz == N / 2) draw_slot_herm<R, N, RL, S, MIX, KS>(v, q, iy, kz, a, d, h0);
-  else draw_slot_plain<R, N, RL, S, MIX, KS>(v, q, iy, kz, a, d, h0);
+  else draw_slot_plain<R, N, RL, S, MIX, KS, XOR3>(v, q, iy, kz, a, d, h0);
 }
 
 // Deterministic counterpart of draw_slot for the Wiener iteration: every mode
