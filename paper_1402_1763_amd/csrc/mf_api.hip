@@ -21,6 +21,7 @@
 
 #include "mf.h"
 #include "plane_kernels.hpp"
+#include "setup_kernels.hpp"
 #include "stream_kernels.hpp"
 #include "sweep_kernels.hpp"
 #include "wiener_kernels.hpp"
@@ -114,6 +115,7 @@ struct Geometry {
   static constexpr int xp_whole = whole_wpp();
   static constexpr int ztiles = (N / mf::ZTile<R, N>::IXB) * (N / mf::ZTile<R, N>::P);
   static constexpr int zept = mf::ZTile<R, N>::EPT;
+  static constexpr int zix = mf::ZTile<R, N>::IXB;
 };
 
 struct Shape {
@@ -127,6 +129,7 @@ struct Shape {
   int xp_whole;                  // whole-pencil x-pass (column) workgroups per kz plane
   int ztiles;                    // z-pass tiles per chain
   int zept;                      // elements per z-pass lane (observation bits per tile)
+  int zix;                       // ix per z-pass tile
 };
 
 template <typename R>
@@ -142,7 +145,7 @@ Shape shape_of(int n) {
                  {G::template x_max_bins<0>(), G::template x_max_bins<1>(),                   \
                   G::template x_max_bins<2>()},                                            \
                  {G::template y_units<0>(), G::template y_units<1>(), G::template y_units<2>()}, \
-                 G::y_rev_distinct() ? 1 : 0, G::xp_whole, G::ztiles, G::zept};           \
+                 G::y_rev_distinct() ? 1 : 0, G::xp_whole, G::ztiles, G::zept, G::zix};   \
   }
     MF_SHAPE(8) MF_SHAPE(16) MF_SHAPE(32) MF_SHAPE(48) MF_SHAPE(64) MF_SHAPE(80) MF_SHAPE(96)
     MF_SHAPE(128) MF_SHAPE(256) MF_SHAPE(512)
@@ -154,7 +157,7 @@ Shape shape_of(int n) {
 struct Layout {
   size_t ctr, tw, qthr, counts, tau, pk, table, status, partials, ratio, gam, tobs, coef, omw, spec,
       staging, rinv, total;
-  size_t spec_elems, spec_stride;
+  size_t spec_elems, spec_stride, staging_bytes;
   int n_wg_split[kTileVariants];   // split x-pass workgroups (one shell partial each) per variant
   int n_wg_whole;                  // whole-pencil x-pass workgroups
   int n_wg_max;
@@ -195,7 +198,10 @@ Layout make_layout(const mf_chain_desc& d) {
   L.coef = take(nc * 2 * m * rs);
   L.omw = take(nc * m * rs);      // tau R^2 / N = 1 - alpha per voxel (Wiener filter only)
   L.spec = take(nc * L.spec_stride * 2 * rs);
-  L.staging = take(m * rs);
+  // the set-up also passes N and d (FP64) through spec and staging, whole z-pass
+  // tiles at a time; on the smallest grids one tile needs more than both
+  L.staging_bytes = std::max(m * rs, 16 * n * n * sh.zix - std::min(16 * n * n * sh.zix, off - L.spec));
+  L.staging = take(L.staging_bytes);
   L.rinv = take(d.has_response ? nc * m * 8 : 0);   // 1 / R per voxel (0 unobserved), FP64
   L.total = off;
   return L;
@@ -236,23 +242,23 @@ std::vector<int32_t> bin_thresholds(int n, int nb) {
   return q;
 }
 
-// Full-grid modes per bin, counted over the half grid with weights 1 on the
-// kz = 0 and kz = N/2 planes and 2 elsewhere.
+// Full-grid modes per bin: over |mx| <= |my| <= |mz| <= N/2, each standing for
+// its permutations and signs (0 and N/2 have one sign).
 std::vector<double> bin_counts(int n, int nb, const std::vector<int32_t>& qthr) {
-  std::vector<long long> cnt(nb, 0);
   const int h = n / 2;
-  std::vector<int> m2(n);
-  for (int i = 0; i < n; ++i) {
-    const int m = i <= h ? i : i - n;
-    m2[i] = m * m;
+  std::vector<int> bin(3 * h * h + 1);   // bin of every q >= 1
+  for (int q = 1, b = 0; q <= 3 * h * h; ++q) {
+    while (b + 1 < nb && qthr[b + 1] <= q) ++b;
+    bin[q] = b;
   }
-  for (int ix = 0; ix < n; ++ix)
-    for (int iy = 0; iy < n; ++iy)
-      for (int kz = 0; kz <= h; ++kz) {
-        const int q = m2[ix] + m2[iy] + kz * kz;
-        if (q == 0) continue;
-        const int b = static_cast<int>(std::upper_bound(qthr.begin(), qthr.end(), q) - qthr.begin()) - 1;
-        cnt[b] += (kz == 0 || kz == h) ? 1 : 2;
+  std::vector<long long> cnt(nb, 0);
+  auto signs = [&](int m) { return m == 0 || m == h ? 1 : 2; };
+  for (int x = 0; x <= h; ++x)
+    for (int y = x; y <= h; ++y)
+      for (int z = y; z <= h; ++z) {
+        if (z == 0) continue;
+        const int perms = x == y ? (y == z ? 1 : 3) : (y == z ? 3 : 6);
+        cnt[bin[x * x + y * y + z * z]] += static_cast<long long>(perms) * signs(x) * signs(y) * signs(z);
       }
   return std::vector<double>(cnt.begin(), cnt.end());
 }
@@ -712,82 +718,99 @@ mf_status download_real(mf_problem* p, double* dst, const void* src, size_t coun
   return MF_OK;
 }
 
-// Voxel i is observed when its noise variance is finite and its response
-// (1 without one) is not zero.
-bool observed(const double* noise_var, const double* response, size_t i) {
-  return !std::isinf(noise_var[i]) && (!response || response[i] != 0.0);
-}
-
-// Messenger coefficients of Sec. 3.1 with T = tau and N~ = N - tau R^2:
-// mean = alpha s + beta with alpha = N~ / N = 1 - tau R^2 / N and
-// beta = tau R d / N; (1, 0) where unobserved.  alpha is 0 in exact
-// arithmetic where N / R^2 is smallest (tau is that minimum); rounding of
-// tau R^2 / N there can leave -1 ulp, which is set back to 0.
-// Also o = tau R^2 / N (0 where unobserved) per voxel, entry order
-// [entry][2], for the Wiener filter's data-dependent coefficients.
-template <typename R, int N>
-void permute_coef(std::vector<R>& out, std::vector<R>& omw, std::vector<uint32_t>& obs,
-                  const double* data, const double* noise_var, const double* response,
-                  double tau) {
-  using T = mf::ZTile<R, N>;
-  const int tiles = (N / T::IXB) * (N / T::P);
-  out.assign(static_cast<size_t>(2) * N * N * N, R(0));
-  omw.assign(static_cast<size_t>(N) * N * N, R(0));
-  obs.assign(tiles, 0);
-  auto resp = [&](size_t i) { return response ? response[i] : 1.0; };
-  auto alpha = [&](size_t i) {
-    return observed(noise_var, response, i)
-               ? std::max(0.0, 1.0 - tau * resp(i) * resp(i) / noise_var[i]) : 1.0;
-  };
-  auto beta = [&](size_t i) {
-    return observed(noise_var, response, i) ? tau * resp(i) * data[i] / noise_var[i] : 0.0;
-  };
-  auto one_minus_alpha = [&](size_t i) {
-    return observed(noise_var, response, i)
-               ? std::min(1.0, tau * resp(i) * resp(i) / noise_var[i]) : 0.0;
-  };
-  for (int tile = 0; tile < tiles; ++tile)
-    for (int e = 0; e < T::EPT; ++e)
-      for (int tid = 0; tid < T::NT; ++tid) {
-        int ix = 0, iya = 0, n = 0;
-        mf::zpass_coef_voxel<R, N>(tile, e, tid, ix, iya, n);
-        const size_t va = (static_cast<size_t>(ix) * N + iya) * N + n, vb = va + N;
-        const size_t entry = (static_cast<size_t>(tile) * T::EPT + e) * T::NT + tid;
-        R* o = &out[entry * 4];
-        o[0] = static_cast<R>(alpha(va));
-        o[1] = static_cast<R>(alpha(vb));
-        o[2] = static_cast<R>(beta(va));
-        o[3] = static_cast<R>(beta(vb));
-        omw[entry * 2] = static_cast<R>(one_minus_alpha(va));
-        omw[entry * 2 + 1] = static_cast<R>(one_minus_alpha(vb));
-        if (observed(noise_var, response, va) || observed(noise_var, response, vb))
-          obs[tile] |= 1u << e;
-      }
-}
-
+// Coefficients, 1 / R and the tiles' observation bits of chain c, formed on the
+// device from the caller's arrays.  N and d pass through the region of the
+// spectra and the state staging, which nothing uses yet, as many planes of ix
+// at a time as fit it; R goes to the place of 1 / R.
 template <typename R>
-mf_status upload_coef(mf_problem* p, int c, const double* data, const double* noise_var,
-                      const double* response, double tau, hipStream_t st) {
-  std::vector<R> buf, omw;
-  std::vector<uint32_t> obs;
-  switch (p->desc.n) {
-#define MF_PERMUTE(NN) \
-  case NN: permute_coef<R, NN>(buf, omw, obs, data, noise_var, response, tau); break;
-    MF_PERMUTE(8) MF_PERMUTE(16) MF_PERMUTE(32) MF_PERMUTE(48) MF_PERMUTE(64) MF_PERMUTE(80)
-    MF_PERMUTE(96) MF_PERMUTE(128) MF_PERMUTE(256) MF_PERMUTE(512)
-#undef MF_PERMUTE
+mf_status setup_coef(mf_problem* p, int c, const double* data, const double* noise_var,
+                     const double* response, double tau, hipStream_t st) {
+  const size_t n = p->desc.n, m = n * n * n;
+  char* stage = p->ws + p->L.spec;
+  const size_t room = p->L.staging + p->L.staging_bytes - p->L.spec;
+  R* coef = reinterpret_cast<R*>(p->ws + p->L.coef) + static_cast<size_t>(c) * 2 * m;
+  R* omw = reinterpret_cast<R*>(p->ws + p->L.omw) + static_cast<size_t>(c) * m;
+  uint32_t* obs = reinterpret_cast<uint32_t*>(p->ws + p->L.tobs) + static_cast<size_t>(c) * p->sh.ztiles;
+  double* rinv = response ? reinterpret_cast<double*>(p->ws + p->L.rinv) + static_cast<size_t>(c) * m : nullptr;
+  MF_HIP(hipMemsetAsync(obs, 0, p->sh.ztiles * 4, st));
+  if (rinv) MF_HIP(hipMemcpyAsync(rinv, response, m * 8, hipMemcpyHostToDevice, st));
+  size_t planes = std::min<size_t>(n, room / (16 * n * n));
+  planes = planes / p->sh.zix * p->sh.zix;   // whole z-pass tiles
+  for (size_t ix = 0; ix < n; ix += planes) {
+    const size_t v0 = ix * n * n, count = std::min(planes, n - ix) * n * n;
+    double* noise_d = reinterpret_cast<double*>(stage);
+    double* data_d = noise_d + count;
+    MF_HIP(hipMemcpyAsync(noise_d, noise_var + v0, count * 8, hipMemcpyHostToDevice, st));
+    MF_HIP(hipMemcpyAsync(data_d, data + v0, count * 8, hipMemcpyHostToDevice, st));
+    const size_t entries = count / 2;
+    const dim3 grid(static_cast<unsigned>((entries + mf::kSetupThreads - 1) / mf::kSetupThreads));
+    switch (p->desc.n) {
+#define MF_COEF(NN)                                                                              \
+  case NN:                                                                                       \
+    hipLaunchKernelGGL((mf::setup_coef_kernel<R, NN>), grid, dim3(mf::kSetupThreads), 0, st,      \
+                       noise_d, rinv ? rinv + v0 : nullptr, data_d, tau, v0, v0 / 2, entries, coef, omw, obs); \
+    break;
+      MF_COEF(8) MF_COEF(16) MF_COEF(32) MF_COEF(48) MF_COEF(64) MF_COEF(80) MF_COEF(96)
+      MF_COEF(128) MF_COEF(256) MF_COEF(512)
+#undef MF_COEF
+    }
+    if (rinv)
+      hipLaunchKernelGGL(mf::setup_rinv_kernel, dim3(1024), dim3(mf::kSetupThreads), 0, st, noise_d,
+                         rinv + v0, count);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(MF_E_DEVICE, "set-up kernel launch failed: %s", hipGetErrorString(e));
   }
-  MF_HIP(hipMemcpyAsync(p->ws + p->L.coef + static_cast<size_t>(c) * buf.size() * sizeof(R),
-                        buf.data(), buf.size() * sizeof(R), hipMemcpyHostToDevice, st));
-  MF_HIP(hipMemcpyAsync(p->ws + p->L.omw + static_cast<size_t>(c) * omw.size() * sizeof(R),
-                        omw.data(), omw.size() * sizeof(R), hipMemcpyHostToDevice, st));
-  MF_HIP(hipMemcpyAsync(p->ws + p->L.tobs + static_cast<size_t>(c) * obs.size() * 4, obs.data(),
-                        obs.size() * 4, hipMemcpyHostToDevice, st));
-  if (p->obs_chunks.size() < static_cast<size_t>(p->desc.n_chains)) p->obs_chunks.resize(p->desc.n_chains);
-  int chunks = 0;
-  for (uint32_t m : obs) chunks += __builtin_popcount(m);
-  p->obs_chunks[c] = chunks;
+  std::vector<uint32_t> bits(p->sh.ztiles);
+  MF_HIP(hipMemcpyAsync(bits.data(), obs, bits.size() * 4, hipMemcpyDeviceToHost, st));
   MF_HIP(hipStreamSynchronize(st));
+  p->obs_chunks.resize(p->desc.n_chains);
+  p->obs_chunks[c] = 0;
+  for (uint32_t b : bits) p->obs_chunks[c] += __builtin_popcount(b);
+  return MF_OK;
+}
+
+// Whether every voxel of a chain passes the checks that scan_chain makes one by
+// one, its smallest observed N / R^2, and whether any voxel is observed.  One
+// pass without branches over groups of 8, which the compiler vectorises (m is
+// a multiple of 512).
+bool clean_chain(const double* data, const double* noise, const double* resp, size_t m, double* tmin,
+                 bool* any) {
+  const double inf = std::numeric_limits<double>::infinity();
+  double t[8], bad[8], seen[8];   // flags as 0 or 1
+  for (int k = 0; k < 8; ++k) t[k] = inf, bad[k] = seen[k] = 0.0;
+  for (size_t i = 0; i < m; i += 8)
+    for (int k = 0; k < 8; ++k) {
+      const double nv = noise[i + k], d = data[i + k], r = resp ? resp[i + k] : 1.0;
+      const bool see = (nv != inf) & (r != 0.0);
+      const double q = resp ? nv / (r * r) : nv;
+      t[k] = see & (q < t[k]) ? q : t[k];
+      seen[k] = see ? 1.0 : seen[k];
+      bad[k] = (r - r != 0.0) | (see & (!(nv > 0.0) | (d - d != 0.0))) ? 1.0 : bad[k];
+    }
+  double all_bad = 0.0, all_seen = 0.0;
+  *tmin = inf;
+  for (int k = 0; k < 8; ++k) {
+    *tmin = std::min(*tmin, t[k]);
+    all_bad += bad[k];
+    all_seen += seen[k];
+  }
+  *any = all_seen > 0.0;
+  return all_bad == 0.0;
+}
+
+// The checks voxel by voxel (Sec. 2: 0 < tau <= N_i / R_i^2 on observed
+// voxels), for the first one that fails.
+mf_status scan_chain(int c, const double* data, const double* noise, const double* resp, size_t m) {
+  for (size_t i = 0; i < m; ++i) {
+    const double nv = noise[i], rr = resp ? resp[i] : 1.0;
+    if (!std::isfinite(rr))
+      return fail(MF_E_NONFINITE, "chain %d voxel %zu: response not finite", c, i);
+    if (rr == 0.0 || (std::isinf(nv) && nv > 0)) continue;
+    if (!(nv > 0.0) || !std::isfinite(nv))
+      return fail(MF_E_NONFINITE, "chain %d voxel %zu: noise variance %g not > 0", c, i, nv);
+    if (!std::isfinite(data[i]))
+      return fail(MF_E_NONFINITE, "chain %d voxel %zu: data not finite", c, i);
+  }
   return MF_OK;
 }
 
@@ -868,22 +891,12 @@ mf_status mf_init_problem(const mf_chain_desc* desc, const double* const* data,
   std::vector<double> tau(nch);
   for (int c = 0; c < nch; ++c) {
     const double* resp = response ? response[c] : nullptr;
-    double tmin = std::numeric_limits<double>::infinity();
-    size_t n_obs = 0;
-    for (size_t i = 0; i < m; ++i) {
-      const double nv = noise_var[c][i];
-      const double rr = resp ? resp[i] : 1.0;
-      if (!std::isfinite(rr))
-        return fail(MF_E_NONFINITE, "chain %d voxel %zu: response not finite", c, i);
-      if (rr == 0.0 || (std::isinf(nv) && nv > 0)) continue;
-      if (!(nv > 0.0) || !std::isfinite(nv))
-        return fail(MF_E_NONFINITE, "chain %d voxel %zu: noise variance %g not > 0", c, i, nv);
-      if (!std::isfinite(data[c][i]))
-        return fail(MF_E_NONFINITE, "chain %d voxel %zu: data not finite", c, i);
-      tmin = std::min(tmin, nv / (rr * rr));
-      ++n_obs;
-    }
-    if (n_obs == 0) return fail(MF_E_INVALID_ARG, "chain %d has no observed voxel", c);
+    double tmin = 0.0;
+    bool any = false;
+    if (!clean_chain(data[c], noise_var[c], resp, m, &tmin, &any) &&
+        (st = scan_chain(c, data[c], noise_var[c], resp, m)) != MF_OK)
+      return st;
+    if (!any) return fail(MF_E_INVALID_ARG, "chain %d has no observed voxel", c);
     if (desc->tau > 0.0) {
       if (desc->tau > tmin)
         return fail(MF_E_TAU, "tau %g exceeds the smallest observed N / R^2 (%g) of chain %d",
@@ -927,24 +940,13 @@ mf_status mf_init_problem(const mf_chain_desc* desc, const double* const* data,
       hipStreamSynchronize(hs) != hipSuccess)
     return cleanup(fail(MF_E_DEVICE, "uploading tables failed"));
   // messenger coefficients in FP64 (alpha = 1 - tau R^2 / N,
-  // beta = tau R d / N), rounded once and stored in the z-pass thread order
+  // beta = tau R d / N), rounded once and stored in the z-pass thread order;
+  // 1 / R per voxel (0 where unobserved) for the Wiener filter
   for (int c = 0; c < nch; ++c) {
     const double* resp = response ? response[c] : nullptr;
-    st = p->fp64() ? upload_coef<double>(p, c, data[c], noise_var[c], resp, tau[c], hs)
-                   : upload_coef<float>(p, c, data[c], noise_var[c], resp, tau[c], hs);
+    st = p->fp64() ? setup_coef<double>(p, c, data[c], noise_var[c], resp, tau[c], hs)
+                   : setup_coef<float>(p, c, data[c], noise_var[c], resp, tau[c], hs);
     if (st != MF_OK) return cleanup(st);
-  }
-  // 1 / R per voxel (0 where unobserved), used by the Wiener filter only
-  if (desc->has_response) {
-    std::vector<double> ri(m);
-    for (int c = 0; c < nch; ++c) {
-      for (size_t i = 0; i < m; ++i)
-        ri[i] = observed(noise_var[c], response[c], i) ? 1.0 / response[c][i] : 0.0;
-      if (hipMemcpyAsync(p->ws + L.rinv + static_cast<size_t>(c) * m * 8, ri.data(), m * 8,
-                         hipMemcpyHostToDevice, hs) != hipSuccess ||
-          hipStreamSynchronize(hs) != hipSuccess)
-        return cleanup(fail(MF_E_DEVICE, "uploading the response failed"));
-    }
   }
   // initial state
   const size_t rs = p->fp64() ? 8 : 4;

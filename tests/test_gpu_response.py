@@ -142,3 +142,24 @@ def test_response_in_fp32_mixing_and_in_a_graph():
     a.close()
     b.close()
     assert na == nb_ == 5 and np.array_equal(sa, sb) and np.array_equal(pa, pb_)
+
+
+@pytest.mark.parametrize("precision,n", [("fp32", 8), ("fp64", 8), ("fp32", 48), ("fp64", 48),
+                                         ("fp32", 80), ("fp32", 96)])
+def test_set_up_in_slabs_matches_oracle(precision, n):
+    """The coefficients formed on the device, in slabs of whole z-pass tiles
+    (one that needs extra room at 8, several at 48 to 96), two chains with
+    different responses: one sweep against the oracle."""
+    w, pb, rs, ds = _response_problem(n, 6, precision, 61, chains=2)
+    smp = binding.Sampler(ds, [pb["noise_var"]] * 2, [pb["pk_init"]] * 2, w.n_bins, w.box,
+                          seed=w.rng_seed, precision=precision, response=rs)
+    smp.sweep(1)
+    for c in range(2):
+        prob = _oracle(w, pb, ds[c], rs[c], chain=c)
+        assert smp.tau(c) == prob.tau
+        st = sampler.run_chain(prob, sampler.State(s=np.zeros((n,) * 3),
+                                                   p_grid=pb["pk_init"] / w.cell_volume), 1)
+        s_gpu, p_gpu, _ = smp.state(c)
+        err_s, err_p = errors(s_gpu, p_gpu, st.s, st.p_grid * w.cell_volume)
+        assert err_s < TOL[precision] and err_p < TOL[precision]
+    smp.close()
