@@ -2246,7 +2246,7 @@ mf_status mf_acf(const double* trace, int32_t t, int32_t n_bins, int32_t max_lag
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const int64_t items = static_cast<int64_t>((n_bins - 1) / mf::kAcfBins + 1) * (max_lag / mf::kAcfLags + 1);
   const unsigned grid = static_cast<unsigned>(std::min<int64_t>(items, 1 << 20));
-  hipLaunchKernelGGL(mf::acf_kernel, dim3(grid), dim3(mf::kWienerThreads), 0, hs, trace, t, n_bins,
+  hipLaunchKernelGGL(mf::acf_kernel, dim3(grid), dim3(mf::kAcfThreads), 0, hs, trace, t, n_bins,
                      max_lag, items, acf);
   hipLaunchKernelGGL(mf::acf_length_kernel, dim3(n_bins), dim3(64), 0, hs, acf, n_bins, max_lag, nc);
   return check_launch("acf");

@@ -232,25 +232,26 @@ moments_kernel(const double* mom, double count, double* mean_out, double* var_ou
 // units once enough workgroups share the work, so a workgroup takes kAcfBins
 // neighbouring bins (64 B of every trace row) and kAcfLags lags and walks the
 // whole series in tiles of kAcfRows rows, the next tile's loads in flight
-// during the products of this one.  32 threads per bin each hold kAcfRun
+// during the products of this one.  The 64 threads of a bin each hold kAcfRun
 // consecutive rows and the kAcfRun + kAcfLags - 1 later rows their lags need:
 // 39 LDS reads for 128 products.  An LDS run of 16 is padded to 17, which puts
 // the 32 threads of a bin on different banks.  All sums run in a fixed order.
-// 8000 samples of 32 bins, 400 lags: 55.8 us a call; one workgroup per bin and
-// whole lags per thread, read from memory, took 2,320 us.  Tiles of 256 rows
-// take 99 us and loads under a condition 115 us: the series is walked tile by
-// tile, and each tile costs one load latency.
-constexpr int kAcfBins = 8, kAcfLags = 8, kAcfRun = 16, kAcfRows = 512;
+// 8000 samples of 32 bins, 400 lags: 48.2 us a call; one workgroup per bin and
+// whole lags per thread, read from memory, took 2,320 us.  The series is walked
+// tile by tile, and each tile costs one load latency: 512 rows by 256 threads
+// take 55.8 us, 256 rows 99 us, and loads under a condition 115 us.
+constexpr int kAcfThreads = 512, kAcfBins = 8, kAcfLags = 8, kAcfRun = 16, kAcfRows = 1024;
 constexpr int kAcfPad = kAcfRows / kAcfRun * (kAcfRun + 1);   // padded rows of one bin
-static_assert(kWienerThreads == kAcfBins * (kAcfRows / kAcfRun), "one run of rows per thread");
+static_assert(kAcfThreads == kAcfBins * (kAcfRows / kAcfRun), "one run of rows per thread");
+static_assert(kAcfThreads / kAcfBins == 64, "one wave per bin");
 
-__global__ void __launch_bounds__(kWienerThreads)
+__global__ void __launch_bounds__(kAcfThreads)
 acf_kernel(const double* trace, int t, int nb, int max_lag, int64_t items, double* acf) {
-  constexpr int ROWS_PER_LOAD = kWienerThreads / kAcfBins;   // 32
+  constexpr int ROWS_PER_LOAD = kAcfThreads / kAcfBins;   // 64
   constexpr int LOADS = kAcfRows / ROWS_PER_LOAD;            // 16
   constexpr int S = kAcfPad + kAcfRun + 1;                   // one more run of later rows
   __shared__ double xa[kAcfBins * S], xw[kAcfBins * S];
-  __shared__ double red[kWienerThreads];
+  __shared__ double red[kAcfThreads];
   const int tid = threadIdx.x;
   const int lrow = tid / kAcfBins, lbin = tid % kAcfBins;    // this thread's loads
   const int cbin = tid / ROWS_PER_LOAD, run = tid % ROWS_PER_LOAD;   // this thread's products
@@ -263,7 +264,7 @@ acf_kernel(const double* trace, int t, int nb, int max_lag, int64_t items, doubl
     // Rows past the end are loaded as the last row and replaced by 0 where they
     // are used: loads under a condition would be waited for one by one.
     auto row_at = [&](int64_t i) { return col[static_cast<size_t>(min(i, static_cast<int64_t>(t) - 1)) * nb]; };
-    // mean of every bin: 32 strided sums, added in order
+    // mean of every bin: 64 strided sums, added in order
     double sum = 0.0;
     for (int64_t i0 = 0; i0 < t; i0 += 32 * ROWS_PER_LOAD) {
       double x[32];
@@ -315,7 +316,6 @@ acf_kernel(const double* trace, int t, int nb, int max_lag, int64_t items, doubl
         for (int j = 0; j < kAcfLags; ++j) acc[j] += x[r] * w[r + j];
       }
     }
-    // the 32 threads of a bin are one half of a wave
 #pragma unroll
     for (int h = ROWS_PER_LOAD / 2; h > 0; h >>= 1) {
       sq += __shfl_xor(sq, h);

@@ -76,10 +76,10 @@ def test_acf_kernel_matches_oracle():
     assert np.array_equal(nc.cpu().numpy(), nc_ref)
 
 
-@pytest.mark.parametrize("t,nb,lag", [(2, 1, 1), (3, 9, 2), (511, 3, 510), (512, 8, 8), (513, 17, 7),
-                                      (600, 8, 16), (1200, 33, 511)])
+@pytest.mark.parametrize("t,nb,lag", [(2, 1, 1), (3, 9, 2), (1023, 3, 1022), (1024, 8, 8), (1025, 17, 7),
+                                      (600, 8, 16), (2200, 33, 1100)])
 def test_acf_at_tile_edges(t, nb, lag):
-    """Series lengths, bin counts and lags around the kernel's tiles of 512
+    """Series lengths, bin counts and lags around the kernel's tiles of 1024
     rows, 8 bins and 8 lags; a constant series gives NaN and no length."""
     import torch
     rng = np.random.default_rng(100 * t + nb)
