@@ -372,6 +372,7 @@ mf::SweepArgs<R> args_of(const mf_problem* p, int path = -1, int xv = -1) {
   a.key1 = static_cast<uint32_t>(p->desc.seed >> 32);
   a.cs = R(1);
   a.cb = R(1);
+  a.rev = 0;
   a.advance = 1;
   a.pk_mode = mf::kPkDraw;
   a.trace = p->diag.trace;
@@ -453,7 +454,7 @@ bool launch_plane_path(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t s
 template <typename R, int N, bool INV, int V, bool RV>
 void launch_ysplit(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   using YS = mf::YSTile<R, N, V>;
-  const int extra = INV ? a.nb : 0;   // the P(k) workgroups
+  const int extra = INV ? mf::pk_blocks(a.nb) : 0;   // the P(k) workgroups
   hipLaunchKernelGGL((mf::ysplit_kernel<R, N, INV, V, RV>),
                      dim3(16 / YS::G * (N / 2 + 1) + extra, 1, nch), dim3(YS::NT), 0, st, a);
 }
@@ -477,7 +478,7 @@ template <typename R, int N, int V>
 void launch_xsplit(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   using XS = mf::XSTile<R, N, V>;
   const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
-  hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXSample, V>), dim3(XS::WPP, N / 2 + 1, nch),
+  hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXSample, V>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
                      dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
 }
 
@@ -540,17 +541,17 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
       break;
     case kXDetK:
       if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXDet, 1>), dim3(XS::WPP, N / 2 + 1, nch),
+        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXDet, 1>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
                            dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
       break;
     case kXMixK:
       if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXMix, 1>), dim3(XS::WPP, N / 2 + 1, nch),
+        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXMix, 1>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
                            dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 2) * sizeof(double) + tables, st, a);
       break;
     case kXMixInvK:
       if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xmixinv_kernel<R, N>), dim3(XS::WPP, N / 2 + 1, nch), dim3(XS::NT),
+        hipLaunchKernelGGL((mf::xmixinv_kernel<R, N>), dim3(XS::WPP * (N / 2 + 1), 1, nch), dim3(XS::NT),
                            a.nb * sizeof(R) + (a.nb + 1) * 4, st, a);
       break;
     case kMixPkK:
@@ -558,7 +559,7 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
       break;
     case kXAdjK:
       if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXAdj, 1>), dim3(XS::WPP, N / 2 + 1, nch),
+        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXAdj, 1>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
                            dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
       break;
     case kX:
@@ -606,14 +607,18 @@ mf_status launch_checked(mf_problem* p, int id, int staging_chain, hipStream_t s
   const int nch = p->desc.n_chains;
   const int xv = path < 0 ? p->xvar : 1, yv = p->yvar + 3 * p->yrad;
   if (path < 0) path = p->xpath;
+  // the rescaling pass of a mixing sweep turns the planes' order round once more
+  const int rev = id == kYI && pk_mode == mf::kPkNone;
   if (p->fp64()) {
     auto a = args_of<double>(p, path, xv);
     a.staging_chain = staging_chain;
+    a.rev = rev;
     a.pk_mode = pk_mode;
     launch<double>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
   } else {
     auto a = args_of<float>(p, path, xv);
     a.staging_chain = staging_chain;
+    a.rev = rev;
     a.pk_mode = pk_mode;
     launch<float>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
   }
@@ -783,7 +788,7 @@ bool clean_chain(const double* data, const double* noise, const double* resp, si
       const double nv = noise[i + k], d = data[i + k], r = resp ? resp[i + k] : 1.0;
       const bool see = (nv != inf) & (r != 0.0);
       const double q = resp ? nv / (r * r) : nv;
-      t[k] = see & (q < t[k]) ? q : t[k];
+      t[k] = (see & (q < t[k])) ? q : t[k];
       seen[k] = see ? 1.0 : seen[k];
       bad[k] = (r - r != 0.0) | (see & (!(nv > 0.0) | (d - d != 0.0))) ? 1.0 : bad[k];
     }
