@@ -482,6 +482,19 @@ void launch_xsplit(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
                      dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
 }
 
+// The mixing sweep's x-pass: two histogram sets, of 8 copies per wave (x tile 0)
+// where both take at most 50 KB of a workgroup's LDS, else of 2 (x tile 1, the
+// same tile otherwise).  256^3 FP32 at 16 bins: 29.6 us with 8 copies, 34.8
+// with 4, 54.0 with 2; a whole mixing sweep of the 64-bin survey 167.6 -> 150.5.
+constexpr int kMixBins8 = 96;
+template <typename R, int N, int V>
+void launch_xmix(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
+  using XS = mf::XSTile<R, N, V>;
+  const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
+  hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXMix, V>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
+                     dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 2) * sizeof(double) + tables, st, a);
+}
+
 // xv, yv: split-path tile variants of the Gibbs x-pass and of the y-passes
 // (yv: units variant + 3 x radix order, launch_ysplit_v); the other x-pass
 // modes (mixing, Wiener) run x-tile variant 1.
@@ -545,9 +558,10 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
                            dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
       break;
     case kXMixK:
-      if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXMix, 1>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
-                           dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 2) * sizeof(double) + tables, st, a);
+      if constexpr (can_split) {
+        if (a.nb <= kMixBins8) launch_xmix<R, N, 0>(a, nch, st);
+        else launch_xmix<R, N, 1>(a, nch, st);
+      }
       break;
     case kXMixInvK:
       if constexpr (can_split)

@@ -513,41 +513,7 @@ __device__ __forceinline__ void advance_sweep(const SweepArgs<R>& a) {
     a.ctr[0] = a.ctr[1] + 1u;
 }
 
-// Truncated normal N(mean, sd^2) restricted to (0, inf), drawn exactly with
-// the words of counter (b 2^16 + j, sweep, kPhaseMix, chain), attempt j.
-// a = -mean/sd is the standardised bound; for a <= 0.5 the proposal is the
-// cosine normal of (x0, x1), accepted when z > a; otherwise Robert's
-// exponential proposal z = a - ln(U23(x0)) / r, r = (a + sqrt(a^2 + 4)) / 2,
-// accepted when U23(x1) <= exp(-(z - r)^2 / 2).  u_mh = U23(x3) of attempt 0
-// is the Metropolis-Hastings uniform.  Returns false after kMixAttempts
-// attempts without a proposal.
-constexpr int kMixAttempts = 64;
-
-__device__ inline bool truncated_normal(double mean, double sd, uint32_t b, uint32_t sweep,
-                                        uint32_t chain, uint32_t k0, uint32_t k1, double& u_new,
-                                        double& u_mh) {
-  const double a = -mean / sd;
-  const double r = 0.5 * (a + sqrt(a * a + 4.0));
-  for (int j = 0; j < kMixAttempts; ++j) {
-    const Words4 w = philox4x32_10(b * 65536u + j, sweep, kPhaseMix, chain, k0, k1);
-    if (j == 0) u_mh = u23<double>(w.x3);
-    double z;
-    bool ok;
-    if (a <= 0.5) {
-      double unused;
-      box_muller(w.x0, w.x1, z, unused);
-      ok = z > a;
-    } else {
-      z = a - log(u23<double>(w.x0)) / r;
-      ok = u23<double>(w.x1) <= exp(-0.5 * (z - r) * (z - r));
-    }
-    if (ok) {
-      u_new = mean + sd * z;
-      return true;
-    }
-  }
-  return false;
-}
+constexpr int kMixAttempts = 64;   // of the truncated normal: one per lane of a wave
 
 // Metropolis-Hastings move of S^_b = M P_b in the mixing sweep (Sec. 3.3,
 // shell form), one workgroup per (bin, chain).  With y = s^/M drawn at the
@@ -558,23 +524,52 @@ __device__ inline bool truncated_normal(double mean, double sd, uint32_t b, uint
 // under Jeffreys' prior, and ~ U^-(2 a0 + 1) exp(-M b0 / U^2) N(U; R/X, T^/X)
 // under the InvGamma(a0, b0) prior; the proposal U' ~ N(R/X, T^/X) truncated
 // to U' > 0 is accepted with probability min(1, U/U'), respectively
-// min(1, (U/U')^(2 a0 + 1) exp(M b0 (1/U^2 - 1/U'^2))) (in logarithms).  Writes the new P, its table and the factor
-// ratio = U'/U (1 if rejected) by which the x-pass output is rescaled.
+// min(1, (U/U')^(2 a0 + 1) exp(M b0 (1/U^2 - 1/U'^2))) (in logarithms).
+// Writes the new P, its table and the factor ratio = U'/U (1 if rejected) by
+// which the x-pass output is rescaled.  Bound by latency: the attempts of the
+// proposal run side by side in a wave's lanes, their logarithms and cosines
+// during the sums' loads.  256^3: 6.9 us, one attempt after the other and two
+// sums in turn 10.2 us.
 template <typename R>
 __global__ void __launch_bounds__(256)
 mix_pk_kernel(SweepArgs<R> a) {
-  __shared__ double red[256];
+  __shared__ double red[256], red2[256];
   const int b = blockIdx.x, c = blockIdx.y, tid = threadIdx.x;
   const size_t off = (static_cast<size_t>(c) * a.nb + b) * a.n_wg_x;
-  const double h1 = sum_partials<256>(a.partials + off, a.n_wg_x, red);
-  __syncthreads();
-  const double h2 = sum_partials<256>(a.partials2 + off, a.n_wg_x, red);
-  if (tid != 0) return;
-  const double m = static_cast<double>(a.m), tau = a.tau[c];
   const uint32_t sweep = a.ctr[1];
+  // what lane j of the first wave makes of the words of attempt j does not
+  // depend on the sums, whose loads are under way meanwhile
+  double s1 = 0.0, s2 = 0.0;
+  for (int w = tid; w < a.n_wg_x; w += 256) {
+    s1 += a.partials[off + w];
+    s2 += a.partials2[off + w];
+  }
+  double z_cos = 0.0, log_u0 = 0.0, u1 = 0.0, u3 = 0.0;
+  if (tid < kMixAttempts) {
+    const Words4 w = philox4x32_10(static_cast<uint32_t>(b) * 65536u + tid, sweep, kPhaseMix,
+                                   a.chain0 + c, a.key0, a.key1);
+    double unused;
+    box_muller(w.x0, w.x1, z_cos, unused);
+    log_u0 = log(u23<double>(w.x0));
+    u1 = u23<double>(w.x1);
+    u3 = u23<double>(w.x3);
+  }
+  red[tid] = s1;
+  red2[tid] = s2;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if (tid < h) {
+      red[tid] += red[tid + h];
+      red2[tid] += red2[tid + h];
+    }
+    __syncthreads();
+  }
+  if (tid >= kMixAttempts) return;
+  const double h1 = red[0], h2 = red2[0];
+  const double m = static_cast<double>(a.m), tau = a.tau[c];
   double* pk = a.pk + static_cast<size_t>(c) * a.nb;
   const double p = pk[b];
-  if (a.trace != nullptr) {
+  if (a.trace != nullptr && tid == 0) {
     const int j = recorded(a, sweep);
     if (j >= 0 && j < a.trace_cap)
       a.trace[(static_cast<size_t>(c) * a.trace_cap + j) * a.nb + b] = p * a.vcell;
@@ -583,9 +578,26 @@ mix_pk_kernel(SweepArgs<R> a) {
   if (a.counts[b] > 0.0 && h1 > 0.0 && p > 0.0) {
     const double u = sqrt(m * p);
     const double xx = m * h1 / p, xt = m * h2 / u;
-    double u_new = 0.0, u_mh = 1.0;
-    bool ok = truncated_normal(xt / xx, sqrt(m * tau / xx), static_cast<uint32_t>(b), sweep,
-                               a.chain0 + c, a.key0, a.key1, u_new, u_mh);
+    // Truncated normal N(mean, sd^2) restricted to (0, inf), drawn exactly with
+    // the words of counter (b 2^16 + j, sweep, kPhaseMix, chain), attempt j: lane
+    // j.  lo = -mean/sd is the standardised bound; for lo <= 0.5 the proposal is
+    // the cosine normal of (x0, x1), accepted when z > lo; otherwise Robert's
+    // exponential proposal z = lo - ln(U23(x0)) / r, r = (lo + sqrt(lo^2 + 4)) / 2,
+    // accepted when U23(x1) <= exp(-(z - r)^2 / 2).  The first accepted attempt
+    // counts; without any the move is rejected.  U23(x3) of attempt 0 is the
+    // Metropolis-Hastings uniform.
+    const double mean = xt / xx, sd = sqrt(m * tau / xx), lo = -mean / sd;
+    const double r = 0.5 * (lo + sqrt(lo * lo + 4.0));
+    double z = z_cos;
+    bool ok = z > lo;
+    if (!(lo <= 0.5)) {
+      z = lo - log_u0 / r;
+      ok = u1 <= exp(-0.5 * (z - r) * (z - r));
+    }
+    const unsigned long long taken = __ballot(ok);
+    ok = taken != 0;
+    const double u_new = mean + sd * __shfl(z, ok ? __ffsll(taken) - 1 : 0);
+    const double u_mh = __shfl(u3, 0);
     if (ok) {
       if (a.prior_a == 0.0 && a.prior_b == 0.0) {
         ok = u_mh <= u / u_new;
@@ -600,11 +612,12 @@ mix_pk_kernel(SweepArgs<R> a) {
       ratio = u_new / u;
     }
     if (!isfinite(p_new) || !(p_new > 0.0) || !isfinite(h1) || !isfinite(h2)) {
-      atomicOr(a.status + c, 1u);
+      if (tid == 0) atomicOr(a.status + c, 1u);
       p_new = p;
       ratio = 1.0;
     }
   }
+  if (tid != 0) return;
   pk[b] = p_new;
   a.ratio[static_cast<size_t>(c) * a.nb + b] = ratio;
   write_table(a.table + static_cast<size_t>(c) * 2 * a.nb, b, p_new, tau, m);
