@@ -2183,13 +2183,13 @@ template <typename R>
 void launch_moments(const mf_problem* p, int chain, double count, double* mean, double* var,
                     hipStream_t st) {
   const int n = p->desc.n;
-  const size_t m = static_cast<size_t>(n) * n * n, entries = m / 2;
+  const size_t m = static_cast<size_t>(n) * n * n;
   const double* mom = p->diag.mom + static_cast<size_t>(chain) * 2 * m;
-  const int nblk = static_cast<int>((entries + mf::kWienerThreads - 1) / mf::kWienerThreads);
   auto go = [&](auto nc) {
     constexpr int N = decltype(nc)::value;
-    hipLaunchKernelGGL((mf::moments_kernel<R, N>), dim3(nblk), dim3(mf::kWienerThreads), 0, st, mom,
-                       count, mean, var, entries);
+    using T = mf::ZTile<R, N>;
+    hipLaunchKernelGGL((mf::moments_kernel<R, N>), dim3(p->sh.ztiles * T::EPT), dim3(T::NT), 0, st, mom,
+                       count, mean, var, m);
   };
   switch (n) {
     case 8: go(std::integral_constant<int, 8>{}); break;

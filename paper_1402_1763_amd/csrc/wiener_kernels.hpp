@@ -208,19 +208,35 @@ __global__ void wiener_grad_pk_kernel(const double* gacc, const double* pkg, dou
 
 // ---------------------------------------------------------------- diagnostics
 // Posterior mean and variance (population form, M2 / K) of a chain's recorded
-// samples, from the z-pass-order Welford sums to [ix][iy][iz].
+// samples, from the z-pass-order Welford sums to [ix][iy][iz].  One workgroup
+// per (z tile, element): its entries are QN neighbouring iz of every row of the
+// tile, turned through LDS so that the stores are runs along iz (128 B at
+// 256^3; stored from the entry order they were single values N rows apart).
+// 256^3: 184 -> 106 us.
 template <typename R, int N>
-__global__ void __launch_bounds__(kWienerThreads)
-moments_kernel(const double* mom, double count, double* mean_out, double* var_out, size_t entries) {
-  const size_t idx = static_cast<size_t>(blockIdx.x) * kWienerThreads + threadIdx.x;
-  if (idx >= entries) return;
-  size_t va = 0, vb = 0;
-  entry_voxels<R, N>(idx, va, vb);
-  const double* m2 = mom + 2 * entries;
-  mean_out[va] = mom[idx * 2];
-  mean_out[vb] = mom[idx * 2 + 1];
-  var_out[va] = m2[idx * 2] / count;
-  var_out[vb] = m2[idx * 2 + 1] / count;
+__global__ void __launch_bounds__((ZTile<R, N>::NT))
+moments_kernel(const double* mom, double count, double* mean_out, double* var_out, size_t m) {
+  using T = ZTile<R, N>;
+  // at N = 8 a thread holds two pencils, and an entry's element half of them
+  constexpr int PENS = T::NT < T::NPEN ? T::NT : T::NPEN;
+  constexpr int QN = T::NT / PENS, ROWS = 2 * PENS, STR = QN + 1;
+  __shared__ double mean_s[ROWS * STR], var_s[ROWS * STR];
+  const int tid = threadIdx.x, tile = blockIdx.x / T::EPT, e = blockIdx.x % T::EPT;
+  const size_t i = (static_cast<size_t>(blockIdx.x) * T::NT + tid) * 2;
+  const int at = tid % PENS * 2 * STR + tid / PENS;
+  mean_s[at] = mom[i];
+  mean_s[at + STR] = mom[i + 1];
+  var_s[at] = mom[m + i] / count;
+  var_s[at + STR] = mom[m + i + 1] / count;
+  __syncthreads();
+  int ix = 0, iya = 0, n0 = 0;
+  zpass_coef_voxel<R, N>(tile, e, 0, ix, iya, n0);   // the tile's first row, the first of its iz
+  for (int it = tid; it < ROWS * QN; it += T::NT) {
+    const int row = it / QN, q = it % QN;            // row = ix of the tile, then iy
+    const size_t v = (static_cast<size_t>(ix + row / T::P) * N + iya + row % T::P) * N + n0 + q;
+    mean_out[v] = mean_s[row * STR + q];
+    var_out[v] = var_s[row * STR + q];
+  }
 }
 
 // Autocorrelation of a recorded chain (Sec. 5.1, Eq. CORR_COEFF) of trace
