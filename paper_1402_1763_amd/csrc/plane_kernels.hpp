@@ -470,7 +470,11 @@ plane_kernel(SweepArgs<R> a) {
 }
 
 // ---------------------------------------------------------------- column
-// P neighbouring iy columns of one kz plane: 256-byte runs where N allows.
+// P neighbouring iy columns of one kz plane: runs of 128 bytes in FP32, 256 in
+// FP64, where N allows.  FP32 takes no radix above 8 at 128 (66 VGPRs: {8, 4, 4}
+// 35.8 us for 8 chains, {16, 8} 44 with 32 columns, 36 with 16; 8 columns 45);
+// the smallest FP64 grids end on radix 2, so that a thread draws two modes
+// instead of four (16^3 7.3 -> 6.1 us, 32^3 8.2 -> 6.5).
 template <int N, bool FP64>
 struct ColRadices;
 #define MF_RADICES(NN, D, COUNT, A, B, C, P_, NT_)                                         \
@@ -487,8 +491,8 @@ MF_RADICES(80, false, 3, 5, 4, 4, 16, 320)
 MF_RADICES(96, false, 3, 6, 4, 4, 16, 384)
 MF_RADICES(128, false, 3, 8, 4, 4, 16, 256)
 MF_RADICES(8, true, 2, 2, 4, 1, 8, 64)
-MF_RADICES(16, true, 2, 4, 4, 1, 16, 64)
-MF_RADICES(32, true, 2, 8, 4, 1, 8, 64)
+MF_RADICES(16, true, 3, 2, 4, 2, 16, 128)
+MF_RADICES(32, true, 3, 4, 4, 2, 8, 128)
 MF_RADICES(48, true, 3, 3, 4, 4, 16, 192)
 MF_RADICES(64, true, 3, 4, 4, 4, 16, 256)
 MF_RADICES(80, true, 3, 5, 4, 4, 16, 320)
@@ -506,10 +510,13 @@ struct ColTile {
   using X = Batch<R, N, Sch, P, NT, true>;
 };
 
-// LDS shell histograms of a column workgroup: hg copies per wave.
+// LDS shell histograms of a column workgroup: 8 copies per wave (by lane)
+// where they take at most 32 KB, else 4, 2 or 1.
 template <typename R, int N>
 __host__ __device__ constexpr int column_hist_copies(int nb) {
-  return ColTile<R, N>::NWAVES * (nb <= 128 ? 4 : 1);
+  int hg = 8;
+  while (hg > 1 && ColTile<R, N>::NWAVES * hg * hist_stride(nb) * 8 > 32768) hg /= 2;
+  return ColTile<R, N>::NWAVES * hg;
 }
 
 template <typename R, int N, int XM>
