@@ -155,13 +155,22 @@ Shape shape_of(int n) {
 }
 
 struct Layout {
-  size_t ctr, tw, qthr, counts, tau, pk, table, status, partials, ratio, gam, tobs, coef, omw, spec,
-      staging, rinv, total;
+  size_t ctr, tw, qthr, counts, tau, pk, table, status, partials, ratio, gam, nrm, tobs, coef, omw,
+      spec, staging, rinv, total;
   size_t spec_elems, spec_stride, staging_bytes;
   int n_wg_split[kTileVariants];   // split x-pass workgroups (one shell partial each) per variant
   int n_wg_whole;                  // whole-pencil x-pass workgroups
   int n_wg_max;
 };
+
+// The column kernel computes the next sweep's messenger normals where the plane
+// kernel occupies at most half of the 256 CUs, in FP64, whose draws take the
+// most instructions.  us per sweep without : with: 16^3 13.5 : 11.8, 32^3 13.9 :
+// 12.6, 64^3 21.1 : 19.0, 80^3 33.2 : 29.5, 128^3 71.1 : 63.6; in FP32 it would
+// cost as much as it gives (64^3 13.0 : 13.0, 96^3 22.3 : 23.2, 128^3 30.4 : 31.0).
+bool draws_ahead(const mf_chain_desc& d) {
+  return d.precision == MF_PREC_FP64 && d.n <= kMaxPlaneN && d.n * d.n_chains <= 128;
+}
 
 Layout make_layout(const mf_chain_desc& d) {
   const bool fp64 = d.precision == MF_PREC_FP64;
@@ -194,6 +203,7 @@ Layout make_layout(const mf_chain_desc& d) {
   L.partials = take(2 * nc * static_cast<size_t>(L.n_wg_max) * nb * 8);   // two sets (mixing)
   L.ratio = take(nc * nb * 8);
   L.gam = take(d.n <= kMaxPlaneN ? mf::kGammaSlots * nc * nb * 8 : 0);
+  L.nrm = take(draws_ahead(d) ? nc * m * rs : 0);
   L.tobs = take(nc * static_cast<size_t>(sh.ztiles) * 4);
   L.coef = take(nc * 2 * m * rs);
   L.omw = take(nc * m * rs);      // tau R^2 / N = 1 - alpha per voxel (Wiener filter only)
@@ -361,6 +371,7 @@ mf::SweepArgs<R> args_of(const mf_problem* p, int path = -1, int xv = -1) {
   a.ctr = reinterpret_cast<uint32_t*>(ws + p->L.ctr);
   a.gam = reinterpret_cast<double*>(ws + p->L.gam);
   a.gam_chains = p->desc.n_chains;
+  a.nrm = draws_ahead(p->desc) ? reinterpret_cast<mf::cx<R>*>(ws + p->L.nrm) : nullptr;
   a.spec_stride = p->L.spec_stride;
   a.m = static_cast<size_t>(p->desc.n) * p->desc.n * p->desc.n;
   a.nb = p->desc.n_bins;
@@ -393,26 +404,31 @@ enum KernelId {
   // sweeps, its parts one by one, the deterministic middle launch, the P(k)
   // workgroups alone, and the column kernel's modes
   kPlaneFirst = 20, kPlaneMid = 21, kPlaneLast = 22, kPlaneZ = 23, kPlaneYF = 24, kPlaneDet = 25,
-  kPlanePk = 26, kColumn = 27, kColumnDet = 28, kColumnAdj = 29, kPlaneMidFull = 30, kPlaneGamma = 31
+  kPlanePk = 26, kColumn = 27, kColumnDet = 28, kColumnAdj = 29, kPlaneMidFull = 30, kPlaneGamma = 31,
+  kColumnAhead = 32
 };
 
 // pk_only, gamma_only: just those workgroups.
-template <typename R, int N, bool YI, int ZMODE, bool YF, bool FULL = false, bool MANY = false>
+template <typename R, int N, bool YI, int ZMODE, bool YF, bool FULL = false, bool MANY = false,
+          bool NORM = false>
 void launch_plane(mf::SweepArgs<R> a, int nch, hipStream_t st, bool pk_only = false,
                   bool gamma_only = false) {
   constexpr int NT = mf::PlaneTile<R, N, MANY>::NT;
   a.gam_wgs = FULL && a.sample_pk ? (static_cast<int>(mf::kGammaAhead) * a.nb + NT - 1) / NT : 0;
   const int grid = a.gam_wgs + (gamma_only ? 0 : (YI ? a.nb : 0) + (pk_only ? 0 : N));
   if (grid > 0)
-    hipLaunchKernelGGL((mf::plane_kernel<R, N, YI, ZMODE, YF, FULL, MANY>), dim3(grid, 1, nch), dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((mf::plane_kernel<R, N, YI, ZMODE, YF, FULL, MANY, NORM>), dim3(grid, 1, nch), dim3(NT),
+                       0, st, a);
 }
 
-template <typename R, int N, int XM>
+template <typename R, int N, int XM, bool AHEAD = false>
 void launch_column(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   using T = mf::ColTile<R, N>;
+  constexpr int per_row = T::NT * (N / T::P);   // threads of a row of workgroups
+  constexpr int ahead = AHEAD ? (N * (N / 2) * (N / 4) + per_row - 1) / per_row : 0;
   const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
   const int copies = XM == mf::kXDet ? 0 : mf::column_hist_copies<R, N>(a.nb);
-  hipLaunchKernelGGL((mf::column_kernel<R, N, XM>), dim3(N / T::P, N / 2 + 1, nch), dim3(T::NT),
+  hipLaunchKernelGGL((mf::column_kernel<R, N, XM, AHEAD>), dim3(N / T::P, N / 2 + 1 + ahead, nch), dim3(T::NT),
                      copies * mf::hist_stride(a.nb) * sizeof(double) + tables, st, a);
 }
 
@@ -423,6 +439,9 @@ void launch_plane_mid(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   using Sch = mf::PlaneRadices<N, sizeof(R) == 8>;
   if constexpr (Sch::nt != Sch::ntb) {
     if (N * nch > 256) return launch_plane<R, N, true, ZMODE, true, false, true>(a, nch, st);
+  }
+  if constexpr (ZMODE == mf::kZSweep && sizeof(R) == 8) {
+    if (a.nrm != nullptr) return launch_plane<R, N, true, ZMODE, true, false, false, true>(a, nch, st);
   }
   launch_plane<R, N, true, ZMODE, true>(a, nch, st);
 }
@@ -444,6 +463,9 @@ bool launch_plane_path(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t s
     case kPlaneDet: launch_plane_mid<R, N, kZDet>(a, nch, st); return true;
     case kPlanePk: launch_plane<R, N, true, kNoZ, false>(a, nch, st, true); return true;
     case kColumn: launch_column<R, N, mf::kXSample>(a, nch, st); return true;
+    case kColumnAhead:
+      if constexpr (sizeof(R) == 8) launch_column<R, N, mf::kXSample, true>(a, nch, st);
+      return true;
     case kColumnDet: launch_column<R, N, mf::kXDet>(a, nch, st); return true;
     case kColumnAdj: launch_column<R, N, mf::kXAdj>(a, nch, st); return true;
   }
@@ -697,13 +719,15 @@ RunPart run_part(const mf_problem* p, int i, uint64_t sweep) {
   return record || i % static_cast<int>(mf::kGammaAhead) == 0 ? kRunNextFull : kRunNext;
 }
 
-mf_status launch_run_part(mf_problem* p, RunPart part, hipStream_t st) {
+// more: another sweep of the run follows (its normals may be drawn now).
+mf_status launch_run_part(mf_problem* p, RunPart part, hipStream_t st, bool more = true) {
   mf_status r = MF_OK;
   if (p->planes()) {
     if (part == kRunEnd) return launch_checked(p, kPlaneLast, 0, st, kPathPlane);
     const int plane = part == kRunFirst ? kPlaneFirst : (part == kRunNext ? kPlaneMid : kPlaneMidFull);
     r = launch_checked(p, plane, 0, st, kPathPlane);
-    return r != MF_OK ? r : launch_checked(p, kColumn, 0, st, kPathPlane);
+    const int column = more && draws_ahead(p->desc) ? kColumnAhead : kColumn;
+    return r != MF_OK ? r : launch_checked(p, column, 0, st, kPathPlane);
   }
   for (int k = 0; k < MF_NUM_KERNELS && part != kRunEnd && r == MF_OK; ++k)
     r = launch_checked(p, kSweepOrder[k], 0, st);
@@ -991,7 +1015,7 @@ mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
   if (room != MF_OK) return room;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   for (int i = 0; i < n_sweeps; ++i) {
-    const mf_status st = launch_run_part(p, run_part(p, i, p->sweep), hs);
+    const mf_status st = launch_run_part(p, run_part(p, i, p->sweep), hs, i + 1 < n_sweeps);
     if (st != MF_OK) return st;
     ++p->sweep;
   }

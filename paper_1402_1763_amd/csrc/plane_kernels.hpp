@@ -223,7 +223,10 @@ enum : int { kNoZ = -1 };   // ZMODE of a plane kernel without its z part
 // sweep and the following ones, kGammaAhead in all, one per thread.  They also
 // have the update of the recorded moments; the launches between leave both out
 // and keep the registers of the transforms.
-template <typename R, int N, bool YI, int ZMODE, bool YF, bool FULL = false, bool MANY = false>
+// With NORM the messenger's normals come from a.nrm, where the column kernel
+// before put them (column_kernel, AHEAD).
+template <typename R, int N, bool YI, int ZMODE, bool YF, bool FULL = false, bool MANY = false,
+          bool NORM = false>
 __global__ void __launch_bounds__((PlaneTile<R, N, MANY>::NT), (PlaneTile<R, N, MANY>::WAVES))
 plane_kernel(SweepArgs<R> a) {
   using T = PlaneTile<R, N, MANY>;
@@ -369,6 +372,19 @@ plane_kernel(SweepArgs<R> a) {
             acc[static_cast<size_t>(j) * 2 + 1] += s[r].y;
           }
           s[r] = cx<R>{a.cs * cf[0] * s[r].x + cb * cf[2], a.cs * cf[1] * s[r].y + cb * cf[3]};
+        }
+      } else if (NORM) {
+        const R tau = static_cast<R>(a.tau[c]);
+        const cx<R>* nrm = a.nrm + static_cast<size_t>(c) * (a.m / 2);
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+          int tile = 0, e = 0;
+          const int j = coef_entry<R, N>(ix, p, q + r * NSL, tile, e);
+          R cf[4] = {R(1), R(1), R(0), R(0)};
+          if (__any(obs[tile] >> e & 1u)) ld4(coef + static_cast<uint32_t>(j) * 4, cf);
+          const cx<R> g = nrm[static_cast<uint32_t>(j)];
+          s[r] = cx<R>{cf[0] * s[r].x + cf[2] + noise_amp(tau * cf[0]) * g.x,
+                       cf[1] * s[r].y + cf[3] + noise_amp(tau * cf[1]) * g.y};
         }
       } else {
         const R tau = static_cast<R>(a.tau[c]);
@@ -519,7 +535,12 @@ __host__ __device__ constexpr int column_hist_copies(int nb) {
   return ColTile<R, N>::NWAVES * hg;
 }
 
-template <typename R, int N, int XM>
+// With AHEAD, rows of workgroups after the planes compute the next sweep's
+// messenger normals into a.nrm, a voxel pair's quads per thread.  A plane kernel
+// of few planes leaves half of the CUs idle and is bound by the vector
+// instructions on the others (10.6 of 20.8 us at 80^3 FP64), of which the draws
+// are the larger part and need nothing of the field.
+template <typename R, int N, int XM, bool AHEAD = false>
 __global__ void __launch_bounds__((ColTile<R, N>::NT))
 column_kernel(SweepArgs<R> a) {
   using T = ColTile<R, N>;
@@ -530,6 +551,31 @@ column_kernel(SweepArgs<R> a) {
   extern __shared__ double dyn[];   // histograms, table (2 nb R), thresholds (nb + 1)
   const int tid = threadIdx.x, nb = a.nb, hs = hist_stride(nb);
   const int iy0 = blockIdx.x * P, kz = blockIdx.y, c = blockIdx.z;
+  if (AHEAD && kz > N / 2) {
+    constexpr int H = N / 2, Q = N / 4;
+    const int k = ((kz - H - 1) * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x)) * NT + tid;
+    if (k >= N * H * Q) return;
+    const int p = k % H, q = k / H % Q, ix = k / (H * Q);
+    const uint32_t wa = static_cast<uint32_t>((ix * N + 2 * p) * Q + q), sweep = a.ctr[1] + 1u;
+    R ga[4], gb[4];
+    {
+      const Words4 w = philox4x32_10(wa, sweep, kPhaseMessenger, a.chain0 + c, a.key0, a.key1);
+      box_muller(w.x0, w.x1, ga[0], ga[1]);
+      box_muller(w.x2, w.x3, ga[2], ga[3]);
+    }
+    {
+      const Words4 w = philox4x32_10(wa + Q, sweep, kPhaseMessenger, a.chain0 + c, a.key0, a.key1);
+      box_muller(w.x0, w.x1, gb[0], gb[1]);
+      box_muller(w.x2, w.x3, gb[2], gb[3]);
+    }
+    cx<R>* nrm = a.nrm + static_cast<size_t>(c) * (a.m / 2);
+#pragma unroll
+    for (int j4 = 0; j4 < 4; ++j4) {
+      int tile = 0, e = 0;
+      nrm[static_cast<uint32_t>(coef_entry<R, N>(ix, p, q + j4 * Q, tile, e))] = cx<R>{ga[j4], gb[j4]};
+    }
+    return;
+  }
   // advance the sweep counter: no column workgroup reads slot 0
   advance_sweep(a);
   cx<R>* spec = a.spec + static_cast<size_t>(c) * a.spec_stride + static_cast<size_t>(kz) * N * N + iy0;

@@ -84,6 +84,9 @@ struct SweepArgs {
   double* gam;            // [kGammaSlots][chain][nb]
   int32_t gam_chains;     // chains of the problem (slot stride / nb)
   int32_t gam_wgs;        // workgroups per chain of this launch that compute kGammaAhead sweeps
+  // Plane path with CUs to spare: the next sweep's messenger normals, in the
+  // order of the coefficients (a voxel pair's two per entry); else nullptr.
+  cx<R>* nrm;             // [chain][m / 2]
   // InvGamma(prior_a, prior_b) prior on P_b, prior_b in grid units; (0, 0) is
   // Jeffreys' prior
   double prior_a, prior_b;
