@@ -245,7 +245,7 @@ mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
  * same state between sweeps, so choices may change at any time.  The
  * default is the split path where it exists, x tile 0 (1 above 255 bins),
  * y group 0 and y_radix 0.  Mixing sweeps always use the split path with x
- * tile 1; the Wiener filter uses the default's schedule.
+ * tile 0 for at most 96 bins, else x tile 1; the Wiener filter uses the default's schedule.
  * mf_set_x_path: MF_E_UNSUPPORTED_SIZE for the split path outside 32..256.
  * mf_set_tuning / mf_get_tuning: the path and the three choices at once;
  *   mf_get_tuning also fills the geometry they stand for.  MF_E_INVALID_ARG

@@ -320,7 +320,7 @@ struct mf_problem {
   int graphs = 0;               // live graphs that captured this problem's sweep
   // Where the plane path is the faster one, by the problem alone (not by the
   // chains of a call), us per sweep against the split path: one FP64 chain of
-  // 16^3 14.5 : 39.8, 32^3 15.5 : 39.8, 80^3 33.1 : 53.7, 128^3 70.8 : 73.5; one
+  // 16^3 11.8 : 39.8, 32^3 12.6 : 39.8, 80^3 29.5 : 53.7, 128^3 63.6 : 73.5; one
   // FP32 chain of 64^3 12.8 : 25.4, 96^3 22.0 : 30.1, 128^3 30.1 : 41.8; 32 FP32
   // chains of 64^3 47.8 : 67.8, 8 of 96^3 60.5 : 69.3, 8 of 128^3 100 : 119.  FP64
   // planes of 96^3 and 128^3 fill a CU's LDS and registers by themselves, so

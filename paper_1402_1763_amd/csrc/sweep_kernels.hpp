@@ -1,4 +1,6 @@
-// Kernels of one Gibbs sweep of the messenger-field sampler (gfx950).
+// Kernels of the four-pass Gibbs sweep of the messenger-field sampler (gfx950),
+// and what the two-pass sweep of grid sides up to 128 (plane_kernels.hpp)
+// shares with it.
 //
 // Device layout of a chain (R = float or double):
 //   coef         z-pass order  R      messenger coefficients (alpha, beta)
@@ -11,7 +13,7 @@
 // (a real-to-half-complex DFT of each z pencil), so keeping the state costs
 // no extra pass.
 //
-// One Gibbs sweep = four launches:
+// One four-pass sweep:
 //   z-pass  : inverse z-DFT (-> s), messenger draw t, forward z-DFT of t
 //   y-pass  : forward y-DFT (and, on the split path, 32 <= N <= 256, the
 //             first half of the forward x-DFT, see "x split")
@@ -636,6 +638,7 @@ __global__ void pk_table_kernel(SweepArgs<R> a) {
 }
 
 // ---------------------------------------------------------------- y-pass
+// Of the whole-pencil path at N = 256 and 512.
 // Workgroup = NPEN consecutive contiguous y pencils (index kz * N + ix).  The
 // inverse pass also carries the sweep's P(k) step: its first nb workgroups of
 // every chain draw one bin each (the x-pass partials are complete when it
@@ -1305,9 +1308,9 @@ xmixinv_kernel(SweepArgs<R> a) {
   for (int j = 0; j < 16; ++j) base[static_cast<size_t>(j) * N] = v[j];
 }
 
-// Whole-transform x-pass (the only path for N = 8, 16, 512; the alternative
-// to the split path elsewhere): workgroup = one kz plane and P
-// consecutive iy columns; forward x-DFT, draw, inverse x-DFT (in the reversed
+// Whole-transform x-pass of N = 256 (the alternative to the split path) and
+// 512 (the only one; up to 128 the column kernel takes its place): workgroup =
+// one kz plane and P consecutive iy columns; forward x-DFT, draw, inverse x-DFT (in the reversed
 // radix order, so it starts from the same registers).
 template <typename R, int N>
 __global__ void __launch_bounds__((XTile<R, N>::NT))
