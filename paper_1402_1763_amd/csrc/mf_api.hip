@@ -436,8 +436,7 @@ void launch_column(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
 // more than the 256 CUs take, or not.
 template <typename R, int N, int ZMODE>
 void launch_plane_mid(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
-  using Sch = mf::PlaneRadices<N, sizeof(R) == 8>;
-  if constexpr (Sch::nt != Sch::ntb) {
+  if constexpr (mf::PlaneTile<R, N>::QUEUES) {
     if (N * nch > 256) return launch_plane<R, N, true, ZMODE, true, false, true>(a, nch, st);
   }
   if constexpr (ZMODE == mf::kZSweep && sizeof(R) == 8) {

@@ -67,6 +67,25 @@ MF_RADICES(128, true, 3, 8, 4, 4, 1024, 1024)
 
 __host__ __device__ constexpr int round_up(int n, int m) { return (n + m - 1) / m * m; }
 
+// The LDS that transforms pass their elements through: p, in one buffer or in
+// two by turns.  With one, every thread must be done reading it (drain) before
+// it is written again; with two, the barrier between writing the other one and
+// reading it says so, too, and half of the barriers go.
+template <class T, int SIZE, bool TWO>
+struct Exchange {
+  T* p;
+  T* other;
+  __device__ __forceinline__ explicit Exchange(T* lds) : p(lds), other(TWO ? lds + SIZE : lds) {}
+  __device__ __forceinline__ void drain() const {
+    if (!TWO) __syncthreads();
+  }
+  __device__ __forceinline__ void turn() {   // before each write
+    T* t = p;
+    p = other;
+    other = t;
+  }
+};
+
 // One batch of NPEN transforms of length N by NT threads, its stages in the
 // schedule's order or (REV) backwards.  PENFAST: neighbouring lanes take
 // neighbouring pencils, else neighbouring butterflies of one pencil.
@@ -156,19 +175,21 @@ struct Batch {
     }
   }
   // The stages after the first, whose results sit in v: through LDS at
-  // idx(pen, pos), which must be free; the last stage's results stay in v.
-  // Other threads may still read the LDS on return.
-  template <bool INV, bool REV, class Idx>
-  __device__ __forceinline__ static void rest(cx<R>* v, const cx<R>* tw, cx<R>* lds, Idx idx) {
-    auto rd = [&](int pen, int pos) { return lds[idx(pen, pos)]; };
-    auto wr = [&](int pen, int pos, cx<R> z) { lds[idx(pen, pos)] = z; };
+  // idx(pen, pos), which must be free with one buffer; the last stage's results
+  // stay in v.  Other threads may still read the LDS on return.
+  template <bool INV, bool REV, class Lds, class Idx>
+  __device__ __forceinline__ static void rest(cx<R>* v, const cx<R>* tw, Lds& lds, Idx idx) {
+    auto rd = [&](int pen, int pos) { return lds.p[idx(pen, pos)]; };
+    auto wr = [&](int pen, int pos, cx<R> z) { lds.p[idx(pen, pos)] = z; };
     if constexpr (STAGES > 1) {
+      lds.turn();
       out<0, REV>(v, wr);
       __syncthreads();
       in<1, INV, REV>(v, tw, rd);
     }
     if constexpr (STAGES > 2) {
-      __syncthreads();
+      lds.drain();
+      lds.turn();
       out<1, REV>(v, wr);
       __syncthreads();
       in<2, INV, REV>(v, tw, rd);
@@ -189,6 +210,15 @@ struct PlaneTile {
   static constexpr int YSTR = N + (N >> PADS), ZSTR = N + 1;
   static constexpr int FIELD = H * (YSTR > ZSTR ? YSTR : ZSTR);
   static constexpr int LDS = FIELD > NT ? FIELD : NT;   // NT: the P(k) sums' reduction
+  // Two exchange buffers where planes do not queue and both fit: us per sweep
+  // with one : two, one chain, 80^3 FP64 29.5 : 28.5, 96^3 FP32 22.4 : 21.4, 128^3
+  // FP32 28.7 : 28.2 (8 chains of 96^3, which lose a CU's second workgroup,
+  // 60.4 : 60.9).
+  static constexpr bool TWO = !MANY && (2 * LDS + 2 * N) * sizeof(cx<R>) <= 160 * 1024;
+  // queues of planes have a kernel of their own: other threads, or two buffers
+  // would leave a CU one workgroup
+  static constexpr bool QUEUES =
+      Sch::nt != Sch::ntb || (TWO && 4 * LDS * sizeof(cx<R>) > 160 * 1024);
   using Y = Batch<R, N, Sch, H, NT, false>;
   using Z = Batch<R, N, Sch, H, NT, true>;
   static constexpr int REGS = Y::REGS > Z::REGS ? Y::REGS : Z::REGS;
@@ -234,10 +264,11 @@ plane_kernel(SweepArgs<R> a) {
   using Z = typename T::Z;
   constexpr int H = N / 2, NT = T::NT;
   constexpr bool ZP = ZMODE != kNoZ;
-  __shared__ cx<R> lds[T::LDS];
+  __shared__ cx<R> field[T::TWO ? 2 * T::LDS : T::LDS];
   __shared__ cx<R> tw[N];
   __shared__ cx<R> row0[N];
   static_assert(T::LDS * sizeof(cx<R>) >= NT * sizeof(double), "reduction space");
+  Exchange<cx<R>, T::LDS, T::TWO> lds(field);
   const int tid = threadIdx.x, c = blockIdx.z;
   int ix = blockIdx.x;
   if (FULL) {
@@ -257,7 +288,7 @@ plane_kernel(SweepArgs<R> a) {
   if (YI) {
     if (ix < a.nb) {
       // with the z part, slot 0 of the counter already counts this sweep
-      pk_draw_block<R, NT, true>(a, ix, c, reinterpret_cast<double*>(lds), ZP ? a.ctr[0] - 1u : a.ctr[1]);
+      pk_draw_block<R, NT, true>(a, ix, c, reinterpret_cast<double*>(field), ZP ? a.ctr[0] - 1u : a.ctr[1]);
       return;
     }
     ix -= a.nb;
@@ -294,8 +325,9 @@ plane_kernel(SweepArgs<R> a) {
             }
           });
     } else {
-      __syncthreads();
-      Y::template out<Y::STAGES - 1, false>(v, [&](int row, int i, cx<R> y) { lds[T::yidx(row, i)] = y; });
+      lds.drain();
+      lds.turn();
+      Y::template out<Y::STAGES - 1, false>(v, [&](int row, int i, cx<R> y) { lds.p[T::yidx(row, i)] = y; });
       __syncthreads();
     }
   }
@@ -311,10 +343,10 @@ plane_kernel(SweepArgs<R> a) {
       Z::template in<0, true, false>(
           v, tw, [&](int p, int k) {
             const int row = k <= H ? k % H : N - k;
-            return pack(k, lds[T::yidx(row, 2 * p)], lds[T::yidx(row, 2 * p + 1)]);
+            return pack(k, lds.p[T::yidx(row, 2 * p)], lds.p[T::yidx(row, 2 * p + 1)]);
           },
           [&](int p, int q, auto bpp, cx<R>* x) {   // k = 0 and k = H share row 0
-            const cx<R> A = lds[T::yidx(0, 2 * p)], B = lds[T::yidx(0, 2 * p + 1)];
+            const cx<R> A = lds.p[T::yidx(0, 2 * p)], B = lds.p[T::yidx(0, 2 * p + 1)];
             if (q == 0) x[0] = cx<R>{A.x, B.x};
             if (q == H % bpp) x[H / bpp] = cx<R>{A.y, B.y};
           });
@@ -326,7 +358,7 @@ plane_kernel(SweepArgs<R> a) {
         return pack(k, A, B);
       });
     }
-    __syncthreads();   // the rows are read, the twiddles written
+    lds.drain();   // the rows are read
     Z::template rest<true, false>(v, tw, lds, zlds);
 
     constexpr int RL = T::RL, NSL = N / RL;
@@ -420,15 +452,16 @@ plane_kernel(SweepArgs<R> a) {
       dft<R, RL, false>(s);
       __builtin_amdgcn_sched_barrier(0);   // one slot's draws at a time: fewer registers
     }
-    __syncthreads();   // every thread is done with the inverse transform's reads
+    lds.drain();   // the inverse transform's reads
     Z::template rest<false, true>(v, tw, lds, zlds);
-    if constexpr (Z::STAGES > 1) __syncthreads();
-    Z::template out<Z::STAGES - 1, true>(v, [&](int p, int k, cx<R> w) { lds[T::zidx(p, k)] = w; });
+    if constexpr (Z::STAGES > 1) lds.drain();
+    lds.turn();
+    Z::template out<Z::STAGES - 1, true>(v, [&](int p, int k, cx<R> w) { lds.p[T::zidx(p, k)] = w; });
     __syncthreads();
     if (!YF) {
       for (int it = tid; it < (H + 1) * H; it += NT) {
         const int k = it / H, p = it % H;
-        const cx<R> u = lds[T::zidx(p, k)], w = lds[T::zidx(p, (N - k) % N)];
+        const cx<R> u = lds.p[T::zidx(p, k)], w = lds.p[T::zidx(p, (N - k) % N)];
         st2(dst + k * ROW + 2 * p, cx<R>{R(0.5) * (u.x + w.x), R(0.5) * (u.y - w.y)},
             cx<R>{R(0.5) * (u.y + w.y), R(0.5) * (w.x - u.x)});
       }
@@ -441,7 +474,7 @@ plane_kernel(SweepArgs<R> a) {
       // W_{N-k}) / (2 i) at odd i; row 0: the real F_0 and F_{N/2}
       Y::template in<0, false, true>(
           v, tw, [&](int row, int i) {
-            const cx<R> u = lds[T::zidx(i / 2, row)], w = lds[T::zidx(i / 2, N - row)];
+            const cx<R> u = lds.p[T::zidx(i / 2, row)], w = lds.p[T::zidx(i / 2, N - row)];
             const bool odd = i % 2 != 0;
             const R a0 = odd ? u.y : u.x, a1 = odd ? w.y : w.x;
             const R b0 = odd ? w.x : u.y, b1 = odd ? u.x : w.y;
@@ -452,11 +485,11 @@ plane_kernel(SweepArgs<R> a) {
 #pragma unroll
             for (int r = 0; r < Y::template radix<true>(0); ++r) {
               const int i = q + r * bpp;
-              const cx<R> u = lds[T::zidx(i / 2, 0)], w = lds[T::zidx(i / 2, H)];
+              const cx<R> u = lds.p[T::zidx(i / 2, 0)], w = lds.p[T::zidx(i / 2, H)];
               x[r] = i % 2 != 0 ? cx<R>{u.y, w.y} : cx<R>{u.x, w.x};
             }
           });
-      __syncthreads();
+      lds.drain();
     } else {
       Y::template in<0, false, true>(
           v, tw, [&](int row, int i) { return src[static_cast<uint32_t>(row * N * N + i)]; },
@@ -465,7 +498,6 @@ plane_kernel(SweepArgs<R> a) {
 #pragma unroll
             for (int r = 0; r < Y::template radix<true>(0); ++r) x[r].y = src[H * ROW + q + r * bpp].x;
           });
-      __syncthreads();   // the twiddles are written
     }
     Y::template rest<false, true>(v, tw, lds, ylds);
     // row 0 goes out as it is, too, and is written again below
@@ -490,7 +522,9 @@ plane_kernel(SweepArgs<R> a) {
 // FP64, where N allows.  FP32 takes no radix above 8 at 128 (66 VGPRs: {8, 4, 4}
 // 35.8 us for 8 chains, {16, 8} 44 with 32 columns, 36 with 16; 8 columns 45);
 // the smallest FP64 grids end on radix 2, so that a thread draws two modes
-// instead of four (16^3 7.3 -> 6.1 us, 32^3 8.2 -> 6.5).
+// instead of four (16^3 7.3 -> 6.1 us, 32^3 8.2 -> 6.5).  One exchange buffer:
+// several workgroups share a CU and cover each other's barriers (two buffers:
+// one chain of 96^3 21.3 against 21.4 us a sweep, 8 of them 61.7 against 60.9).
 template <int N, bool FP64>
 struct ColRadices;
 #define MF_RADICES(NN, D, COUNT, A, B, C, P_, NT_)                                         \
@@ -546,7 +580,8 @@ column_kernel(SweepArgs<R> a) {
   using T = ColTile<R, N>;
   using X = typename T::X;
   constexpr int P = T::P, NT = T::NT, RL = T::RL, NSL = N / RL;
-  __shared__ cx<R> lds[P * T::STR];
+  __shared__ cx<R> field[P * T::STR];
+  Exchange<cx<R>, P * T::STR, false> lds(field);
   __shared__ cx<R> tw[N];
   extern __shared__ double dyn[];   // histograms, table (2 nb R), thresholds (nb + 1)
   const int tid = threadIdx.x, nb = a.nb, hs = hist_stride(nb);
@@ -612,7 +647,7 @@ column_kernel(SweepArgs<R> a) {
     }
     dft<R, RL, true>(x);
   }
-  __syncthreads();   // every thread is done with the forward transform's reads
+  lds.drain();   // the forward transform's reads
   X::template rest<true, true>(v, tw, lds, idx);
   X::template out<X::STAGES - 1, true>(v, [&](int col, int i, cx<R> z) { spec[static_cast<uint32_t>(i * N + col)] = z; });
   if constexpr (XM != kXDet) {

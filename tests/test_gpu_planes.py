@@ -33,7 +33,8 @@ def _samplers(n, precision, chains, count):
 
 # a few planes, and more planes than CUs (other workgroups at 80 and 128)
 @pytest.mark.parametrize("n,precision,chains", [(8, "fp64", 2), (16, "fp64", 1), (48, "fp32", 3),
-                                                (80, "fp32", 4), (80, "fp64", 1), (96, "fp32", 1),
+                                                (80, "fp32", 4), (80, "fp64", 1), (80, "fp64", 4),
+                                                (96, "fp32", 1), (96, "fp32", 3),
                                                 (128, "fp32", 3), (128, "fp64", 1)])
 def test_a_run_of_sweeps_equals_single_sweeps(n, precision, chains):
     """35 sweeps (the P draws' gamma variates are computed 32 sweeps ahead) in
