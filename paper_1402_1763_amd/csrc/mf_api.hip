@@ -320,9 +320,9 @@ struct mf_problem {
   int graphs = 0;               // live graphs that captured this problem's sweep
   // Where the plane path is the faster one, by the problem alone (not by the
   // chains of a call), us per sweep against the split path: one FP64 chain of
-  // 16^3 11.8 : 39.8, 32^3 12.6 : 39.8, 80^3 29.5 : 53.7, 128^3 63.6 : 73.5; one
-  // FP32 chain of 64^3 12.8 : 25.4, 96^3 22.0 : 30.1, 128^3 30.1 : 41.8; 32 FP32
-  // chains of 64^3 47.8 : 67.8, 8 of 96^3 60.5 : 69.3, 8 of 128^3 100 : 119.  FP64
+  // 16^3 11.8 : 39.8, 32^3 12.5 : 39.8, 80^3 28.6 : 53.7, 128^3 63.6 : 73.5; one
+  // FP32 chain of 64^3 12.8 : 25.4, 96^3 21.4 : 30.1, 128^3 28.2 : 41.8; 32 FP32
+  // chains of 64^3 46.8 : 67.8, 8 of 96^3 60.4 : 69.3, 8 of 128^3 100 : 119.  FP64
   // planes of 96^3 and 128^3 fill a CU's LDS and registers by themselves, so
   // queues of them do not overlap: 8 chains of 96^3 157 : 152, 4 of 128^3 170 : 165.
   bool prefers_planes() const {
