@@ -399,8 +399,8 @@ def bench_mixing(args):
 def wiener_grad_bytes(n: int, real_bytes: int, n_bins: int, n_iter: int, every: int,
                       coef_frac: float = 1.0) -> int:
     """Algorithmic HBM bytes of one chi2 forward + backward run of the
-    messenger Wiener filter (K iterations, checkpoint every E): K plain
-    iterations, K recomputed ones that store t^, K adjoint iterations that
+    messenger Wiener filter on the two-pass schedule (K iterations,
+    checkpoint every E): K plain iterations, K recomputed ones that store t^, K adjoint iterations that
     read it back and accumulate the adjoint field, plus set-up and read-out.
     coef_frac: share of the coefficients the z-pass reads (tiles with an
     observed voxel)."""
@@ -411,15 +411,14 @@ def wiener_grad_bytes(n: int, real_bytes: int, n_bins: int, n_iter: int, every: 
     field = real_bytes * m                         # one real field
     n_wg_x = (n // 2 + 1) * (n // x_columns(n))
     partials = 2 * n_wg_x * n_bins * 8
-    n_ckpt = -(-n_iter // every)
-    plain = 8 * spec + zcoef                       # z, y, x, y passes
+    plain = 4 * spec + zcoef                       # plane and column passes
     store = plain + spec                           # + t^ written
     adjoint = plain + spec + 2 * field + partials  # + t^ read, adjoint field summed
     forward_extra = (coef + 8 * m + coef           # data -> (alpha, beta)
-                     + spec + 2 * spec * n_ckpt    # zero start, checkpoint copies
+                     + spec                        # zero start (checkpoints are left in place)
                      + spec + field                # s_K read-out
                      + coef + 8 * m + field)       # chi2
-    backward_extra = (field + spec + 2 * spec * n_ckpt   # zeroing, checkpoint restores
+    backward_extra = (field + spec                       # zeroing
                       + spec + field                     # s_K read-out
                       + spec + 2 * field                 # last adjoint field summed
                       + coef + 8 * m + 2 * field + 8 * m)  # d chi2 / d d
