@@ -317,10 +317,10 @@ mf_status mf_debug_spectrum(mf_problem* p, int32_t chain, double* buf, int32_t t
 
 /* Graphs of sweeps, for batches of problems (different grid sizes or
  * precisions) run as independent chains (Sec. 3.4: independent chains need no
- * communication).  mf_graph_create captures one Gibbs sweep of each of the n
- * problems into one HIP graph; problems are independent branches of the graph
- * and may run concurrently.  mf_graph_launch replays it n_sweeps times on
- * `stream` (asynchronously) and advances every problem's sweep counter; the
+ * communication).  mf_graph_create captures Gibbs sweeps of each of the n
+ * problems into HIP graphs (one sweep, and several at a time); problems are
+ * independent branches of a graph and may run concurrently.  mf_graph_launch
+ * replays n_sweeps sweeps on `stream` (asynchronously) and advances every problem's sweep counter; the
  * replays draw the same random numbers as mf_gibbs_sweep would.  The problems
  * must outlive the graph and must not be swept on another stream while a
  * replay is in flight.  A graph replays the diagnostic recording set when it
