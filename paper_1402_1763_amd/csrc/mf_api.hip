@@ -318,6 +318,9 @@ struct mf_problem {
   int xvar = 0, yvar = 0;       // split-path tile variants of Gibbs sweeps (autotuner)
   int yrad = 0;                 // 1: the split y-passes run their radix stages reversed
   int graphs = 0;               // live graphs that captured this problem's sweep
+  // Sweeps of this problem were captured by its caller: replays move the device's
+  // sweep index without the host's, which then says nothing about the next sweep.
+  bool captured = false;
   // Where the plane path is the faster one, by the problem alone (not by the
   // chains of a call), us per sweep against the split path: one FP64 chain of
   // 16^3 11.8 : 39.8, 32^3 12.5 : 39.8, 80^3 28.6 : 53.7, 128^3 63.6 : 73.5; one
@@ -710,12 +713,24 @@ mf_status launch_sweep_kernel(mf_problem* p, int k, hipStream_t st) {
 enum RunPart : int { kRunFirst, kRunNext, kRunNextFull, kRunEnd };
 
 // Part of the i-th sweep of a run, whose index is `sweep`: one with recorded
-// moments takes the full plane kernel, too.
+// moments takes the full plane kernel, too, and so does every sweep of a
+// problem whose index the host does not know (the kernel decides by the
+// device's).
 RunPart run_part(const mf_problem* p, int i, uint64_t sweep) {
   if (i == 0) return kRunFirst;
   const DiagRec& d = p->diag;
-  const bool record = d.mom != nullptr && sweep >= d.start && (sweep - d.start) % d.thin == 0;
+  const bool record = d.mom != nullptr &&
+                      (p->captured || (sweep >= d.start && (sweep - d.start) % d.thin == 0));
   return record || i % static_cast<int>(mf::kGammaAhead) == 0 ? kRunNextFull : kRunNext;
+}
+
+// Notes whether the stream is being captured by the caller (never the null
+// stream, which cannot be).
+void note_capture(mf_problem* p, hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (st != nullptr && !p->captured && hipStreamIsCapturing(st, &status) == hipSuccess &&
+      status != hipStreamCaptureStatusNone)
+    p->captured = true;
 }
 
 // more: another sweep of the run follows (its normals may be drawn now).
@@ -1013,6 +1028,7 @@ mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
   const mf_status room = check_sweep_room(p, n_sweeps);
   if (room != MF_OK) return room;
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  note_capture(p, hs);
   for (int i = 0; i < n_sweeps; ++i) {
     const mf_status st = launch_run_part(p, run_part(p, i, p->sweep), hs, i + 1 < n_sweeps);
     if (st != MF_OK) return st;
@@ -1033,6 +1049,7 @@ mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
   const mf_status room = check_sweep_room(p, n_sweeps);
   if (room != MF_OK) return room;
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  note_capture(p, hs);
   const int ids[6] = {kZ, kYF, kXMixK, kMixPkK, kXMixInvK, kYI};
   for (int i = 0; i < n_sweeps; ++i) {
     for (int id : ids) {
