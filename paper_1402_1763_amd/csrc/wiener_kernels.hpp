@@ -280,20 +280,22 @@ acf_kernel(const double* trace, int t, int nb, int max_lag, int64_t items, doubl
     // Rows past the end are loaded as the last row and replaced by 0 where they
     // are used: loads under a condition would be waited for one by one.
     auto row_at = [&](int64_t i) { return col[static_cast<size_t>(min(i, static_cast<int64_t>(t) - 1)) * nb]; };
-    // mean of every bin: 64 strided sums, added in order
+    // mean of every bin, counted from its first sample so that the mean of a
+    // constant series is that sample exactly: 64 strided sums, added in order
+    const double x0 = col[0];
     double sum = 0.0;
     for (int64_t i0 = 0; i0 < t; i0 += 32 * ROWS_PER_LOAD) {
       double x[32];
 #pragma unroll
       for (int k = 0; k < 32; ++k) x[k] = row_at(i0 + lrow + k * ROWS_PER_LOAD);
 #pragma unroll
-      for (int k = 0; k < 32; ++k) sum += i0 + lrow + k * ROWS_PER_LOAD < t ? x[k] : 0.0;
+      for (int k = 0; k < 32; ++k) sum += i0 + lrow + k * ROWS_PER_LOAD < t ? x[k] - x0 : 0.0;
     }
     red[tid] = sum;
     __syncthreads();
     double mu = 0.0;
     for (int r = 0; r < ROWS_PER_LOAD; ++r) mu += red[r * kAcfBins + lbin];
-    mu /= t;
+    mu = x0 + mu / t;
     auto slot = [](int row) { return row + row / kAcfRun; };
     double acc[kAcfLags] = {0.0}, sq = 0.0;
     double pa[LOADS], pw[LOADS + 1];

@@ -96,6 +96,19 @@ def test_acf_at_tile_edges(t, nb, lag):
     tol = 100 * t * 2.0 ** -53 * t / (t - np.arange(lag + 1))[:, None]
     assert np.all(np.abs(c - c_ref)[~np.isnan(c_ref)] <= np.broadcast_to(tol, c.shape)[~np.isnan(c_ref)])
 
+@pytest.mark.parametrize("value", [0.1, 1.0 / 3.0, 2.7e3, 3.0e-5, -1.0e7 / 3.0])
+def test_acf_of_a_constant_series_is_nan(value):
+    """P held fixed records a constant series, whatever its value: NaN at every
+    lag and no correlation length, beside a bin that does vary."""
+    import torch
+    for t in (2, 8, 50, 1000, 2200):
+        x = np.full((t, 3), value)
+        x[:, 1] += np.arange(t)
+        c, nc = binding.acf(torch.from_numpy(x).cuda(), t // 2)
+        c, nc = c.cpu().numpy(), nc.cpu().numpy()
+        assert np.isnan(c[:, [0, 2]]).all() and np.isfinite(c[:, 1]).all(), (value, t)
+        assert nc[0] == nc[2] == -1
+
 
 def test_graph_replays_record_too():
     w = workloads.small_workload(32, 8, precision="fp32", seed=71, rng_seed=72)
