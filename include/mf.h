@@ -135,7 +135,12 @@ mf_status mf_init_problem(const mf_chain_desc* desc, const double* const* data,
  * The sweep index is Philox counter word 1 (32 bits): sweeps that would take
  * it beyond 2^32 - 1 are refused, since they would repeat the random numbers
  * of earlier sweeps.  This holds for every call that sweeps.
- * Errors: MF_E_INVALID_ARG (also that bound), MF_E_DEVICE. */
+ * The sweeps may be captured by the caller: replays draw by the sweep index on
+ * the device, and mf_set_chain_state brings the host's count in line.
+ * Where a launch of the two-pass sweep (mf_set_x_path) fails, the next call
+ * that uses the field first completes the sweep that was cut short and ends the
+ * run, on its own stream (MF_E_STATE while that is being captured).
+ * Errors: MF_E_INVALID_ARG (also that bound), MF_E_STATE, MF_E_DEVICE. */
 mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
 
 /* As mf_gibbs_sweep, but times the kernels with HIP events, synchronises,

@@ -321,6 +321,12 @@ struct mf_problem {
   // Sweeps of this problem were captured by its caller: replays move the device's
   // sweep index without the host's, which then says nothing about the next sweep.
   bool captured = false;
+  // What a run of the two-pass sweep still owes the field where one of its
+  // launches failed: the rest of a sweep, or the end of the run (the last P draw
+  // and the inverse y transform).  The next call that uses the field launches it
+  // first (settle).
+  enum Owed { kNothing, kOwesColumn, kOwesEnd };
+  Owed owed = kNothing;
   // Where the plane path is the faster one, by the problem alone (not by the
   // chains of a call), us per sweep against the split path: one FP64 chain of
   // 16^3 11.8 : 39.8, 32^3 12.5 : 39.8, 80^3 28.6 : 53.7, 128^3 63.6 : 73.5; one
@@ -724,27 +730,54 @@ RunPart run_part(const mf_problem* p, int i, uint64_t sweep) {
   return record || i % static_cast<int>(mf::kGammaAhead) == 0 ? kRunNextFull : kRunNext;
 }
 
-// Notes whether the stream is being captured by the caller (never the null
-// stream, which cannot be).
-void note_capture(mf_problem* p, hipStream_t st) {
+// Whether the caller is capturing the stream (never the null stream, which
+// cannot be); noted in the problem.
+bool note_capture(mf_problem* p, hipStream_t st) {
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  if (st != nullptr && !p->captured && hipStreamIsCapturing(st, &status) == hipSuccess &&
-      status != hipStreamCaptureStatusNone)
-    p->captured = true;
+  const bool on = st != nullptr && hipStreamIsCapturing(st, &status) == hipSuccess &&
+                  status != hipStreamCaptureStatusNone;
+  if (on) p->captured = true;
+  return on;
 }
 
-// more: another sweep of the run follows (its normals may be drawn now).
-mf_status launch_run_part(mf_problem* p, RunPart part, hipStream_t st, bool more = true) {
+// more: another sweep of the run follows (its normals may be drawn now).  owed
+// (nullptr while capturing): what the field is owed after the launches made.
+mf_status launch_run_part(mf_problem* p, RunPart part, hipStream_t st, bool more = true,
+                          mf_problem::Owed* owed = nullptr) {
   mf_status r = MF_OK;
   if (p->planes()) {
-    if (part == kRunEnd) return launch_checked(p, kPlaneLast, 0, st, kPathPlane);
-    const int plane = part == kRunFirst ? kPlaneFirst : (part == kRunNext ? kPlaneMid : kPlaneMidFull);
-    r = launch_checked(p, plane, 0, st, kPathPlane);
-    const int column = more && draws_ahead(p->desc) ? kColumnAhead : kColumn;
-    return r != MF_OK ? r : launch_checked(p, column, 0, st, kPathPlane);
+    auto step = [&](int id, mf_problem::Owed then) {
+      if (r == MF_OK) r = launch_checked(p, id, 0, st, kPathPlane);
+      if (r == MF_OK && owed != nullptr) *owed = then;
+    };
+    if (part == kRunEnd) {
+      step(kPlaneLast, mf_problem::kNothing);
+      return r;
+    }
+    step(part == kRunFirst ? kPlaneFirst : (part == kRunNext ? kPlaneMid : kPlaneMidFull),
+         mf_problem::kOwesColumn);
+    step(more && draws_ahead(p->desc) ? kColumnAhead : kColumn, mf_problem::kOwesEnd);
+    return r;
   }
   for (int k = 0; k < MF_NUM_KERNELS && part != kRunEnd && r == MF_OK; ++k)
     r = launch_checked(p, kSweepOrder[k], 0, st);
+  return r;
+}
+
+// Completes a run that a failed launch cut short: the sweep it was in, then its
+// end.  A captured launch would be repeated with every replay: refused.
+mf_status settle(mf_problem* p, hipStream_t st) {
+  if (p->owed == mf_problem::kNothing) return MF_OK;
+  if (note_capture(p, st))
+    return fail(MF_E_STATE, "an earlier sweep failed: complete it outside the capture first");
+  if (p->owed == mf_problem::kOwesColumn) {
+    const mf_status r = launch_checked(p, kColumn, 0, st, kPathPlane);
+    if (r != MF_OK) return r;
+    p->owed = mf_problem::kOwesEnd;
+    ++p->sweep;
+  }
+  const mf_status r = launch_checked(p, kPlaneLast, 0, st, kPathPlane);
+  if (r == MF_OK) p->owed = mf_problem::kNothing;
   return r;
 }
 
@@ -1025,16 +1058,17 @@ mf_status mf_init_problem(const mf_chain_desc* desc, const double* const* data,
 mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
   if (!p) return fail(MF_E_INVALID_ARG, "problem is NULL");
   if (n_sweeps < 0) return fail(MF_E_INVALID_ARG, "negative sweep count");
-  const mf_status room = check_sweep_room(p, n_sweeps);
-  if (room != MF_OK) return room;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  note_capture(p, hs);
+  mf_status st = settle(p, hs);
+  if (st == MF_OK) st = check_sweep_room(p, n_sweeps);
+  if (st != MF_OK) return st;
+  mf_problem::Owed* owed = note_capture(p, hs) ? nullptr : &p->owed;
   for (int i = 0; i < n_sweeps; ++i) {
-    const mf_status st = launch_run_part(p, run_part(p, i, p->sweep), hs, i + 1 < n_sweeps);
-    if (st != MF_OK) return st;
+    if ((st = launch_run_part(p, run_part(p, i, p->sweep), hs, i + 1 < n_sweeps, owed)) != MF_OK)
+      return st;
     ++p->sweep;
   }
-  return n_sweeps > 0 ? launch_run_part(p, kRunEnd, hs) : MF_OK;
+  return n_sweeps > 0 ? launch_run_part(p, kRunEnd, hs, false, owed) : MF_OK;
 }
 
 mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
@@ -1046,9 +1080,10 @@ mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
   // the mixing sweep's Metropolis-Hastings move is a move of P itself
   if (!p->desc.sample_pk)
     return fail(MF_E_INVALID_ARG, "mixing sweeps update P(k); the problem holds P fixed (sample_pk = 0)");
-  const mf_status room = check_sweep_room(p, n_sweeps);
-  if (room != MF_OK) return room;
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  mf_status room = settle(p, hs);
+  if (room == MF_OK) room = check_sweep_room(p, n_sweeps);
+  if (room != MF_OK) return room;
   note_capture(p, hs);
   const int ids[6] = {kZ, kYF, kXMixK, kMixPkK, kXMixInvK, kYI};
   for (int i = 0; i < n_sweeps; ++i) {
@@ -1079,7 +1114,8 @@ mf_status timed_sweeps(mf_problem* p, int32_t n_sweeps, hipStream_t hs, double* 
                        int32_t n_kernels, void* evict, size_t evict_bytes, int evict_mode) {
   if (!p || !kernel_ms || n_kernels < 0) return fail(MF_E_INVALID_ARG, "bad argument");
   if (n_sweeps <= 0) return fail(MF_E_INVALID_ARG, "need at least one sweep");
-  const mf_status room = check_sweep_room(p, n_sweeps);
+  mf_status room = settle(p, hs);
+  if (room == MF_OK) room = check_sweep_room(p, n_sweeps);
   if (room != MF_OK) return room;
   const size_t half16 = evict_bytes / 32;   // 16-byte vectors per half
   // every event created is destroyed on every way out
@@ -1159,6 +1195,8 @@ mf_status mf_get_chain_state(mf_problem* p, int32_t chain, double* s_out, double
   if (chain < 0 || chain >= p->desc.n_chains) return fail(MF_E_STATE, "chain %d out of range", chain);
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const size_t m = static_cast<size_t>(p->desc.n) * p->desc.n * p->desc.n;
+  const mf_status whole = settle(p, hs);
+  if (whole != MF_OK) return whole;
   if (s_out) {
     mf_status st = launch_checked(p, kZGet, chain, hs);
     if (st != MF_OK) return st;
@@ -1190,6 +1228,8 @@ mf_status mf_set_chain_state(mf_problem* p, int32_t chain, const double* s, cons
       if (!std::isfinite(s[i])) return fail(MF_E_NONFINITE, "s not finite at %zu", i);
   const mf_status chk = check_sweep_index(sweep);
   if (chk != MF_OK) return chk;
+  const mf_status whole = settle(p, static_cast<hipStream_t>(stream));
+  if (whole != MF_OK) return whole;
   p->sweep = sweep;
   const mf_status st = write_counter(p, sweep, static_cast<hipStream_t>(stream));
   if (st != MF_OK) return st;
@@ -1219,6 +1259,8 @@ mf_status mf_save_checkpoint(mf_problem* p, int32_t chain, void* buf, size_t byt
   if (chain < 0 || chain >= p->desc.n_chains) return fail(MF_E_STATE, "chain %d out of range", chain);
   if (bytes < checkpoint_bytes(p)) return fail(MF_E_INVALID_ARG, "checkpoint buffer too small");
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  const mf_status whole = settle(p, hs);
+  if (whole != MF_OK) return whole;
   const size_t rs = p->fp64() ? 8 : 4;
   CheckpointHeader h{};
   std::memcpy(h.magic, "MFGIBBS1", 8);
@@ -1250,6 +1292,9 @@ mf_status mf_load_checkpoint(mf_problem* p, int32_t chain, const void* buf, size
     return fail(MF_E_INVALID_ARG, "checkpoint does not match this problem");
   if (check_sweep_index(h.sweep) != MF_OK) return MF_E_INVALID_ARG;
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  if (p->desc.n_chains == 1) p->owed = mf_problem::kNothing;   // all of it is replaced
+  const mf_status whole = settle(p, hs);
+  if (whole != MF_OK) return whole;
   const size_t rs = p->fp64() ? 8 : 4;
   const int nb = p->desc.n_bins;
   const char* in = static_cast<const char*>(buf);
@@ -1437,6 +1482,7 @@ mf_status mf_autotune(mf_problem* p, int32_t trials, void* stream, double* ms, m
   p->xvar = xv0;
   p->yvar = yv0;
   p->yrad = yr0;
+  p->owed = mf_problem::kNothing;   // every chain is replaced
   for (int c = 0; c < p->desc.n_chains; ++c) {
     const mf_status r = mf_load_checkpoint(p, c, saved[c].data(), cb, stream);
     if (st == MF_OK) st = r;
@@ -1478,7 +1524,8 @@ mf_status mf_debug_run_kernel(mf_problem* p, int32_t kernel, uint64_t sweep, voi
   if (kernel < 0 || kernel >= MF_NUM_KERNELS) return fail(MF_E_INVALID_ARG, "bad kernel id");
   if (check_sweep_index(sweep) != MF_OK) return MF_E_INVALID_ARG;
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  const mf_status st = write_counter(p, sweep, hs);
+  mf_status st = settle(p, hs);
+  if (st == MF_OK) st = write_counter(p, sweep, hs);
   if (st != MF_OK) return st;
   // the split path shows its own four kernels, also where its sweeps run planes;
   // a plane path's last kernel alone has no earlier one to compute its gammas
@@ -1495,6 +1542,8 @@ mf_status mf_debug_spectrum(mf_problem* p, int32_t chain, double* buf, int32_t t
   if (!p || !buf) return fail(MF_E_INVALID_ARG, "NULL argument");
   if (chain < 0 || chain >= p->desc.n_chains) return fail(MF_E_STATE, "chain %d out of range", chain);
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  const mf_status whole = settle(p, hs);
+  if (whole != MF_OK) return whole;
   const size_t count = 2 * p->L.spec_elems;
   const size_t rs = p->fp64() ? 8 : 4;
   char* dev = p->ws + p->L.spec + static_cast<size_t>(chain) * p->L.spec_stride * 2 * rs;
@@ -1522,6 +1571,7 @@ struct mf_graph {
   // Without a plane path every sweep is a first one, and there is no end.
   hipGraph_t graph[kGraphParts] = {};
   hipGraphExec_t exec[kGraphParts] = {};
+  std::vector<bool> planes;   // whether a problem's branch runs the two-pass sweep
   bool counted = false;   // probs' graph counts include this graph
   ~mf_graph() {
     if (counted)
@@ -1572,7 +1622,10 @@ mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, 
   g->side.push_back(cap);
   hs = cap;
   bool any_planes = false;
-  for (int i = 0; i < n; ++i) any_planes |= problems[i]->planes();
+  for (int i = 0; i < n; ++i) {
+    g->planes.push_back(problems[i]->planes());
+    any_planes |= problems[i]->planes();
+  }
   for (int part = kRunFirst; part < kGraphParts; ++part) {
     if (part != kRunFirst && part != kGraphMany && !any_planes) continue;
     if ((e = hipStreamBeginCapture(hs, hipStreamCaptureModeThreadLocal)) != hipSuccess)
@@ -1608,11 +1661,12 @@ mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, 
 mf_status mf_graph_launch(mf_graph* g, int32_t n_sweeps, void* stream) {
   if (!g) return fail(MF_E_INVALID_ARG, "graph is NULL");
   if (n_sweeps < 0) return fail(MF_E_INVALID_ARG, "negative sweep count");
+  hipStream_t hs = static_cast<hipStream_t>(stream);
   for (auto* p : g->probs) {
-    const mf_status room = check_sweep_room(p, n_sweeps);
+    mf_status room = settle(p, hs);
+    if (room == MF_OK) room = check_sweep_room(p, n_sweeps);
     if (room != MF_OK) return room;
   }
-  hipStream_t hs = static_cast<hipStream_t>(stream);
   const bool planes = g->exec[kRunEnd] != nullptr;
   auto part_of = [&](int i) {   // the fullest that a problem's i-th sweep needs
     int part = planes ? kRunFirst : kRunNext;
@@ -1620,15 +1674,21 @@ mf_status mf_graph_launch(mf_graph* g, int32_t n_sweeps, void* stream) {
       for (auto* p : g->probs) part = std::max<int>(part, run_part(p, i, p->sweep + i));
     return part;
   };
-  for (int i = 0; i < n_sweeps;) {
+  hipError_t e = hipSuccess;
+  int i = 0;
+  while (i < n_sweeps && e == hipSuccess) {
     int same = 0;   // plain further sweeps from here on
     while (same < kGraphSweeps && i + same < n_sweeps && part_of(i + same) == kRunNext) ++same;
     const bool many = same == kGraphSweeps;
-    MF_HIP(hipGraphLaunch(g->exec[many ? kGraphMany : (planes ? part_of(i) : kRunFirst)], hs));
-    i += many ? kGraphSweeps : 1;
+    e = hipGraphLaunch(g->exec[many ? kGraphMany : (planes ? part_of(i) : kRunFirst)], hs);
+    if (e == hipSuccess) i += many ? kGraphSweeps : 1;
   }
-  if (n_sweeps > 0 && g->exec[kRunEnd]) MF_HIP(hipGraphLaunch(g->exec[kRunEnd], hs));
-  for (auto* p : g->probs) p->sweep += static_cast<uint64_t>(n_sweeps);
+  if (n_sweeps > 0 && e == hipSuccess && planes) e = hipGraphLaunch(g->exec[kRunEnd], hs);
+  for (size_t k = 0; k < g->probs.size(); ++k) {
+    g->probs[k]->sweep += static_cast<uint64_t>(i);
+    if (e != hipSuccess && i > 0 && g->planes[k]) g->probs[k]->owed = mf_problem::kOwesEnd;
+  }
+  MF_HIP(e);
   return MF_OK;
 }
 

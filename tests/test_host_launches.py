@@ -1,0 +1,136 @@
+"""CPU tests of which kernels the library launches: tests/hip_stub.cpp stands in
+for the HIP runtime in a child process, so no device is needed and no kernel
+runs."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, os
+import numpy as np
+from paper_1402_1763_amd import binding
+lib = binding.load()
+stub = ctypes.CDLL(os.environ["HIP_STUB"])
+stub.stub_log.restype = ctypes.c_char_p
+
+def log():
+    out = stub.stub_log().decode().splitlines()
+    stub.stub_reset()
+    return out
+
+def problem(n, precision="fp32", chains=1, nb=8, sample_pk=True):
+    desc = binding.make_desc(n, nb, 10.0 * n, 1, precision, sample_pk=sample_pk, n_chains=chains)
+    size = binding.mf_workspace_bytes(desc)
+    ws = np.zeros(size + 256, dtype=np.uint8)
+    ptr = (ws.ctypes.data + 255) // 256 * 256
+    one = np.ones((n, n, n))
+    h = binding.mf_init_problem(desc, [one] * chains, [one] * chains, [np.ones(nb)] * chains, None, ptr, size, 0)
+    problem.keep.append(ws)
+    stub.stub_reset()
+    return h
+problem.keep = []
+
+def names(lines):
+    return [l.split(" grid ")[0] for l in lines]
+
+def sweep(h, n, stream=0):
+    return lib.mf_gibbs_sweep(ctypes.c_void_p(h), n, ctypes.c_void_p(stream))
+
+def state(h):
+    return lib.mf_get_chain_state(ctypes.c_void_p(h), 0, binding._dptr(np.zeros(1 << 22)), None, None, None)
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    stub = str(tmp_path_factory.mktemp("stub") / "libhipstub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC",
+                    os.path.join(ROOT, "tests", "hip_stub.cpp"), "-o", stub], check=True)
+
+    def go(body):
+        env = dict(os.environ, LD_PRELOAD=stub, HIP_STUB=stub, PYTHONPATH=ROOT)
+        res = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body)], cwd=ROOT, env=env,
+                             capture_output=True, text=True, timeout=300)
+        assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-3000:]
+        return res.stdout
+    return go
+
+
+@pytest.mark.parametrize("n,precision,nth", [(n, p, k) for n, p in ((16, "fp64"), (64, "fp32"), (96, "fp32"))
+                                             for k in range(7)])
+def test_a_run_cut_short_is_completed_by_the_next_call(run, n, precision, nth):
+    """Launch `nth` of the 7 of a three-sweep run fails: the state call that
+    follows launches what the field is owed (the column of the sweep it was in,
+    the run's end) before it reads the field, once."""
+    out = run(f"""
+        h = problem({n}, "{precision}")
+        sweep(h, 3)
+        whole = names(log())
+        assert len(whole) == 7 and [k.split("_")[0] for k in whole] == ["plane", "column"] * 3 + ["plane"]
+        end = whole[-1]
+        h = problem({n}, "{precision}")
+        stub.stub_fail_launch({nth})
+        assert sweep(h, 3) == binding.MF_E_DEVICE
+        assert names(log()) == whole[:{nth}]
+        # the first retry fails, too, unless nothing is owed: reported, and owed still
+        if {nth} > 0:
+            stub.stub_fail_launch(0)
+            assert state(h) == binding.MF_E_DEVICE and log() == []
+        assert state(h) == 0
+        got = names(log())
+        column = got[0] if {nth} % 2 == 1 and {nth} < 6 else None
+        want = ([column] if column else []) + ([end] if {nth} > 0 else [])
+        assert got[:-1] == want and got[-1].startswith("zpass_kernel"), (got, want)
+        assert column is None or column.startswith("column_kernel")
+        assert state(h) == 0 and len(log()) == 1       # nothing owed any more
+        _, _, done = binding.mf_get_chain_state(h, 0, {n}, 8, 0, True)
+        assert done == ({nth} + 1) // 2, done
+    """)
+    print(out)
+
+
+def test_every_call_on_the_field_completes_a_run_first(run):
+    """Sweeps, mixing sweeps, checkpoints and new states of one chain of several
+    do so; a checkpoint into the only chain replaces the field instead."""
+    run("""
+        def broken(chains=1):
+            h = problem(64, chains=chains)
+            stub.stub_fail_launch(2)
+            assert sweep(h, 3) == binding.MF_E_DEVICE
+            log()
+            return h
+        end = "plane_kernel<float, 64, true, -1, false"
+        h = broken(); sweep(h, 1); assert log()[0].startswith(end)
+        h = broken(); assert lib.mf_mixing_sweep(ctypes.c_void_p(h), 1, None) == 0; assert log()[0].startswith(end)
+        h = broken(); binding.mf_gibbs_sweep_timed(h, 1, 0); assert log()[0].startswith(end)
+        h = broken(); blob = binding.mf_save_checkpoint(h, 0, 0); assert log()[0].startswith(end)
+        h = broken(2); binding.mf_load_checkpoint(h, 1, blob, 0); assert log()[0].startswith(end)
+        h = broken(1); binding.mf_load_checkpoint(h, 0, blob, 0); assert not any(l.startswith(end) for l in log())
+        assert state(h) == 0 and len(log()) == 1
+        h = broken(); binding.mf_set_chain_state(h, 0, None, np.ones(8), 5, 0); assert log()[0].startswith(end)
+        h = broken(); binding.mf_debug_spectrum(h, 0, 64, stream=0); assert log()[0].startswith(end)
+        h = broken(); g = binding.mf_graph_create([h], 0); log()
+        binding.mf_graph_launch(g, 1, 0); assert log()[0].startswith(end)
+        # not inside a capture, where every replay would repeat it
+        h = broken(); stub.stub_caller_captures(1)
+        assert sweep(h, 1, stream=8) == binding.MF_E_STATE and log() == []
+    """)
+
+
+def test_a_graph_launch_that_fails_counts_and_completes_its_sweeps(run):
+    run("""
+        h = problem(64)
+        g = binding.mf_graph_create([h], 0)
+        log()
+        stub.stub_fail_launch(2)                     # the third replay
+        assert lib.mf_graph_launch(ctypes.c_void_p(g), 6, None) == binding.MF_E_DEVICE
+        ran = sum(" " == l[0] and "column" in l for l in log())
+        assert ran > 0
+        assert state(h) == 0 and log()[0].startswith("plane_kernel<float, 64, true, -1, false")
+        assert binding.mf_get_chain_state(h, 0, 64, 8, 0, False)[2] == ran
+    """)
