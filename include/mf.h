@@ -229,11 +229,7 @@ mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
  * Path 1 (whole): the x-pass runs whole x pencils through LDS.  It is the
  * only path for N = 8, 16, 512.  Up to N = 128 a run of n whole-path sweeps
  * joins the y-passes between its x-passes with the z-pass (a (kz, iy) plane
- * fits the LDS of a CU): 2 n + 1 launches.  The split path with its three
- * choices at their defaults stands for the library's faster one there, which
- * up to N = 128 is the same two-pass sweep (except FP64 problems of 96^3 and
- * 128^3 with more than 256 planes of constant ix); other choices run the split
- * path itself.
+ * fits the LDS of a CU): the two-pass sweep, 2 n + 1 launches.
  * On the split path three choices are open:
  *  - x_tile: the x-pass workgroup (variant 0 is the library's tile rule,
  *    e.g. 128 iy columns x 2 k1 values at 256, with 8 LDS shell histograms
@@ -247,13 +243,16 @@ mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
  *    schedule (e.g. 6 x 4 x 4 at 96), 1 its reverse (4 x 4 x 6).
  * Every choice gives the same chain up to rounding (the shell sums are
  * grouped by workgroup, the transforms factor differently) and leaves the
- * same state between sweeps, so choices may change at any time.  The
- * default is the split path where it exists, x tile 0 (1 above 255 bins),
- * y group 0 and y_radix 0.  Mixing sweeps always use the split path with x
+ * same state between sweeps, so choices may change at any time.  The default is
+ * the library's faster path: up to N = 128 the whole path's two-pass sweep
+ * (except FP64 problems of 96^3 and 128^3 with more than 256 planes of constant
+ * ix), at other sides the split path where it exists, with x tile 0 (1 above 255
+ * bins), y group 0 and y_radix 0.  Mixing sweeps always use the split path with x
  * tile 0 for at most 96 bins, else x tile 1; the Wiener filter uses the default's schedule.
  * mf_set_x_path: MF_E_UNSUPPORTED_SIZE for the split path outside 32..256.
  * mf_set_tuning / mf_get_tuning: the path and the three choices at once;
- *   mf_get_tuning also fills the geometry they stand for.  MF_E_INVALID_ARG
+ *   mf_get_tuning also fills the geometry they stand for (0 on the whole
+ *   path, which has none of these choices).  MF_E_INVALID_ARG
  *   for a variant outside 0..2, a y_radix other than 0 or 1, or an x tile
  *   whose histograms cannot hold the problem's bins, MF_E_UNSUPPORTED_SIZE
  *   as mf_set_x_path.

@@ -59,9 +59,10 @@ bool supported(int n) {
 // y-passes carry its radix-N/16 half, and the x-pass runs 16-point DFTs in
 // registers.  kPathWhole: whole x pencils through LDS.  kPathPlane (N <= 128):
 // whole x pencils, with the z and y transforms of a plane in one kernel
-// (plane_kernels.hpp); not a caller's choice but what the whole path, and the
-// split path with the default tiles, run where it exists.  All leave the same
-// state between sweeps, so a problem may switch.
+// (plane_kernels.hpp); it is what the whole path runs where it exists, and, as a
+// problem's own path, the default there: reported as the whole path, while
+// mf_debug_run_kernel shows such a problem's four split kernels.  All leave the
+// same state between sweeps, so a problem may switch.
 enum XPath : int { kPathSplit = 0, kPathWhole = 1, kPathPlane = 2 };
 constexpr int kMaxPlaneN = 128;
 
@@ -337,13 +338,16 @@ struct mf_problem {
   bool prefers_planes() const {
     return desc.n <= kMaxPlaneN && !(fp64() && desc.n >= 96 && desc.n * desc.n_chains > 256);
   }
-  // The Gibbs sweep runs the plane kernels: on the whole path, and where they
-  // are preferred on the split path with nothing chosen away from its defaults.
-  bool planes() const {
-    if (xpath == kPathWhole) return desc.n <= kMaxPlaneN;
-    return prefers_planes() && xvar == default_xvar() && yvar == 0 && yrad == 0;
+  bool can_split() const { return desc.n >= 32 && desc.n <= 256; }
+  // The path of a problem whose caller has not chosen one.
+  int default_path() const {
+    return !can_split() ? kPathWhole : (prefers_planes() ? kPathPlane : kPathSplit);
   }
+  // The Gibbs sweep runs the plane kernels.
+  bool planes() const { return xpath != kPathSplit && desc.n <= kMaxPlaneN; }
   int sweep_path() const { return planes() ? kPathPlane : xpath; }
+  // The path of the four kernels one by one.
+  int kernel_path() const { return xpath == kPathPlane ? kPathSplit : xpath; }
   // x-pass workgroups of a path; the split path's with x-tile variant xv
   int n_wg(int path, int xv) const { return path == kPathSplit ? L.n_wg_split[xv] : L.n_wg_whole; }
   // the default split x tile: 8 histogram copies per wave where they fit
@@ -357,7 +361,7 @@ namespace {
 // and split x-tile variant xv (< 0: the problem's Gibbs variant).
 template <typename R>
 mf::SweepArgs<R> args_of(const mf_problem* p, int path = -1, int xv = -1) {
-  if (path < 0) path = p->xpath;
+  if (path < 0) path = p->kernel_path();
   if (xv < 0) xv = p->xvar;
   mf::SweepArgs<R> a{};
   char* ws = p->ws;
@@ -650,7 +654,7 @@ mf_status launch_checked(mf_problem* p, int id, int staging_chain, hipStream_t s
                          int pk_mode = mf::kPkDraw) {
   const int nch = p->desc.n_chains;
   const int xv = path < 0 ? p->xvar : 1, yv = p->yvar + 3 * p->yrad;
-  if (path < 0) path = p->xpath;
+  if (path < 0) path = p->kernel_path();
   // the rescaling pass of a mixing sweep turns the planes' order round once more
   const int rev = id == kYI && pk_mode == mf::kPkNone;
   if (p->fp64()) {
@@ -1007,7 +1011,7 @@ mf_status mf_init_problem(const mf_chain_desc* desc, const double* const* data,
   p->ws = static_cast<char*>(workspace);
   p->tau = tau;
   p->sweep = 0;
-  p->xpath = (n >= 32 && n <= 256) ? kPathSplit : kPathWhole;
+  p->xpath = p->default_path();
   p->xvar = p->default_xvar();
   hipStream_t hs = static_cast<hipStream_t>(stream);
 
@@ -1320,7 +1324,7 @@ mf_status mf_set_x_path(mf_problem* p, int32_t path) {
 
 mf_status mf_get_x_path(const mf_problem* p, int32_t* path) {
   if (!p || !path) return fail(MF_E_INVALID_ARG, "NULL argument");
-  *path = p->xpath;
+  *path = p->xpath == kPathSplit ? kPathSplit : kPathWhole;
   return MF_OK;
 }
 
@@ -1344,7 +1348,7 @@ mf_status mf_set_tuning(mf_problem* p, const mf_tuning* t) {
 
 mf_status mf_get_tuning(const mf_problem* p, mf_tuning* t) {
   if (!p || !t) return fail(MF_E_INVALID_ARG, "NULL argument");
-  t->x_path = p->xpath;
+  t->x_path = p->xpath == kPathSplit ? kPathSplit : kPathWhole;
   t->x_tile = p->xvar;
   t->y_group = p->yvar;
   const bool split = p->xpath == kPathSplit;
@@ -1396,8 +1400,7 @@ mf_status mf_autotune(mf_problem* p, int32_t trials, void* stream, double* ms, m
   if (trials < 1) return fail(MF_E_INVALID_ARG, "need at least one trial sweep");
   const double nan = std::numeric_limits<double>::quiet_NaN();
   for (int i = 0; i < MF_TUNE_SLOTS; ++i) ms[i] = nan;
-  const bool can_split = p->desc.n >= 32 && p->desc.n <= 256;
-  if (!can_split) {
+  if (!p->can_split()) {
     p->xpath = kPathWhole;
     p->xvar = p->default_xvar();
     p->yvar = 0;
@@ -1527,14 +1530,13 @@ mf_status mf_debug_run_kernel(mf_problem* p, int32_t kernel, uint64_t sweep, voi
   mf_status st = settle(p, hs);
   if (st == MF_OK) st = write_counter(p, sweep, hs);
   if (st != MF_OK) return st;
-  // the split path shows its own four kernels, also where its sweeps run planes;
   // a plane path's last kernel alone has no earlier one to compute its gammas
   if (p->xpath == kPathWhole && p->planes() && kernel == MF_NUM_KERNELS - 1) {
     const mf_status g = launch_checked(p, kPlaneGamma, 0, hs, kPathPlane);
     if (g != MF_OK) return g;
   }
-  return p->xpath == kPathSplit ? launch_checked(p, kSweepOrder[kernel], 0, hs)
-                                : launch_sweep_kernel(p, kernel, hs);
+  return p->kernel_path() == kPathSplit ? launch_checked(p, kSweepOrder[kernel], 0, hs)
+                                        : launch_sweep_kernel(p, kernel, hs);
 }
 
 mf_status mf_debug_spectrum(mf_problem* p, int32_t chain, double* buf, int32_t to_device,

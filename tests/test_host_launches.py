@@ -134,3 +134,57 @@ def test_a_graph_launch_that_fails_counts_and_completes_its_sweeps(run):
         assert state(h) == 0 and log()[0].startswith("plane_kernel<float, 64, true, -1, false")
         assert binding.mf_get_chain_state(h, 0, 64, 8, 0, False)[2] == ran
     """)
+
+
+def test_a_path_chosen_is_the_path_run_timed_and_reported(run):
+    """The default up to 128^3 is the two-pass sweep, reported as the whole path;
+    the split path with its default tiles can be chosen, is reported with its
+    geometry and is what the autotuner times against the whole path.  Setting
+    what is reported changes nothing."""
+    run("""
+        def tuning(h):
+            t = binding.mf_tuning()
+            assert lib.mf_get_tuning(ctypes.c_void_p(h), ctypes.byref(t)) == 0
+            path = ctypes.c_int32(-1)
+            assert lib.mf_get_x_path(ctypes.c_void_p(h), ctypes.byref(path)) == 0
+            assert path.value == t.x_path
+            return t
+        def choose(h, t):
+            assert lib.mf_set_tuning(ctypes.c_void_p(h), ctypes.byref(t)) == 0
+        def kinds(h):
+            stub.stub_reset()
+            assert sweep(h, 2) == 0
+            return [k.split("_")[0] for k in names(log())]
+        planes = ["plane", "column", "plane", "column", "plane"]
+        split = ["zpass", "ysplit", "xsplit", "ysplit"] * 2
+        for n, precision, chains, default in ((64, "fp32", 1, planes), (128, "fp32", 1, planes), (96, "fp64", 2, planes),
+                                              (96, "fp64", 3, split), (16, "fp32", 1, planes)):
+            h = problem(n, precision, chains)
+            assert kinds(h) == default, (n, precision, chains)
+            t = tuning(h)
+            assert t.x_path == (0 if default is split else 1)
+            assert (t.x_cols > 0) == (t.y_units > 0) == (default is split)
+            choose(h, t)
+            assert kinds(h) == default
+            if n == 16:
+                continue
+            choose(h, binding.mf_tuning(x_path=0))
+            t = tuning(h)
+            assert t.x_path == 0 and t.x_cols > 0 and t.x_k1 > 0 and t.x_hist == 8 and t.y_units > 0
+            assert kinds(h) == split
+            choose(h, binding.mf_tuning(x_path=1))
+            assert tuning(h).x_path == 1 and tuning(h).x_cols == 0 and kinds(h) == planes
+        # four kernels one by one, in the split form, for a problem without a choice
+        h = problem(64)
+        for k in range(4):
+            binding.mf_debug_run_kernel(h, k, 0, 0)
+        assert [k.split("_")[0] for k in names(log())] == split[:4]
+        # every x tile is timed on the split path, and planes for the whole path only
+        h = problem(64)
+        ms = (ctypes.c_double * 10)()
+        assert lib.mf_autotune(ctypes.c_void_p(h), 5, None, ms, None) == 0
+        runs = names(log())
+        for v in range(3):
+            assert sum(k == f"xsplit_kernel<float, 64, 0, {v}>" for k in runs) >= 18, v
+        assert sum(k.startswith("column") for k in runs) == 3 * 6
+    """)
