@@ -384,6 +384,7 @@ mf::SweepArgs<R> args_of(const mf_problem* p, int path = -1, int xv = -1) {
   a.ctr = reinterpret_cast<uint32_t*>(ws + p->L.ctr);
   a.gam = reinterpret_cast<double*>(ws + p->L.gam);
   a.gam_chains = p->desc.n_chains;
+  a.gam_sweeps = 1;
   a.nrm = draws_ahead(p->desc) ? reinterpret_cast<mf::cx<R>*>(ws + p->L.nrm) : nullptr;
   a.spec_stride = p->L.spec_stride;
   a.m = static_cast<size_t>(p->desc.n) * p->desc.n * p->desc.n;
@@ -414,23 +415,23 @@ enum KernelId {
   kZ = 0, kYF = 1, kX = 2, kYI = 3, kZSet = 10, kZGet = 11, kTable = 12,
   kZDetK = 13, kZAccK = 14, kXDetK = 15, kXAdjK = 16, kXMixK = 17, kMixPkK = 18, kXMixInvK = 19,
   // plane path: the plane kernel's first, middle and last launch of a run of
-  // sweeps, its parts one by one, the deterministic middle launch, the P(k)
-  // workgroups alone, and the column kernel's modes
-  kPlaneFirst = 20, kPlaneMid = 21, kPlaneLast = 22, kPlaneZ = 23, kPlaneYF = 24, kPlaneDet = 25,
-  kPlanePk = 26, kColumn = 27, kColumnDet = 28, kColumnAdj = 29, kPlaneMidFull = 30, kPlaneGamma = 31,
-  kColumnAhead = 32
+  // sweeps (kPlaneMidRec: of a recorded sweep; kPlaneMidFull: with gamma
+  // variates, too), its parts one by one, the deterministic middle launch, the
+  // P(k) and gamma workgroups alone, and the column kernel's modes
+  kPlaneFirst = 20, kPlaneMid = 21, kPlaneMidRec = 22, kPlaneMidFull = 23, kPlaneLast = 24, kPlaneZ = 25,
+  kPlaneYF = 26, kPlaneDet = 27, kPlanePk = 28, kPlaneGamma = 29, kColumn = 30, kColumnDet = 31,
+  kColumnAdj = 32, kColumnAhead = 33
 };
 
 // pk_only, gamma_only: just those workgroups.
-template <typename R, int N, bool YI, int ZMODE, bool YF, bool FULL = false, bool MANY = false,
-          bool NORM = false>
+template <typename R, int N, bool YI, int ZMODE, bool YF, int X = 0, bool MANY = false, bool NORM = false>
 void launch_plane(mf::SweepArgs<R> a, int nch, hipStream_t st, bool pk_only = false,
                   bool gamma_only = false) {
   constexpr int NT = mf::PlaneTile<R, N, MANY>::NT;
-  a.gam_wgs = FULL && a.sample_pk ? (static_cast<int>(mf::kGammaAhead) * a.nb + NT - 1) / NT : 0;
+  a.gam_wgs = (X & mf::kWithGammas) && a.sample_pk ? (a.gam_sweeps * a.nb + NT - 1) / NT : 0;
   const int grid = a.gam_wgs + (gamma_only ? 0 : (YI ? a.nb : 0) + (pk_only ? 0 : N));
   if (grid > 0)
-    hipLaunchKernelGGL((mf::plane_kernel<R, N, YI, ZMODE, YF, FULL, MANY, NORM>), dim3(grid, 1, nch), dim3(NT),
+    hipLaunchKernelGGL((mf::plane_kernel<R, N, YI, ZMODE, YF, X, MANY, NORM>), dim3(grid, 1, nch), dim3(NT),
                        0, st, a);
 }
 
@@ -445,17 +446,21 @@ void launch_column(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
                      copies * mf::hist_stride(a.nb) * sizeof(double) + tables, st, a);
 }
 
-// The launches that a run repeats, with the workgroup for the number of planes:
-// more than the 256 CUs take, or not.
-template <typename R, int N, int ZMODE>
-void launch_plane_mid(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
+// The launches that a run repeats, and its last, with the workgroup for the
+// number of planes: more than the 256 CUs take, or not.  (The last launch with
+// the queues' workgroup, us per single sweep, FP32: 8 chains of 80^3 53.5 :
+// 51.3, of 96^3 73.5 : 70.5, of 128^3 121.6 : 119.4; the first launch and those
+// of recorded sweeps are no faster with it: 8 chains of 96^3 68.5 : 70.5 and
+// 88.4 : 91.4.)
+template <typename R, int N, int ZMODE, bool YF = true>
+void launch_plane_sized(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   if constexpr (mf::PlaneTile<R, N>::QUEUES) {
-    if (N * nch > 256) return launch_plane<R, N, true, ZMODE, true, false, true>(a, nch, st);
+    if (N * nch > 256) return launch_plane<R, N, true, ZMODE, YF, 0, true>(a, nch, st);
   }
   if constexpr (ZMODE == mf::kZSweep && sizeof(R) == 8) {
-    if (a.nrm != nullptr) return launch_plane<R, N, true, ZMODE, true, false, false, true>(a, nch, st);
+    if (a.nrm != nullptr) return launch_plane<R, N, true, ZMODE, YF, 0, false, true>(a, nch, st);
   }
-  launch_plane<R, N, true, ZMODE, true>(a, nch, st);
+  launch_plane<R, N, true, ZMODE, YF>(a, nch, st);
 }
 
 // The plane path's kernels; false for an id of another path.
@@ -464,16 +469,18 @@ bool launch_plane_path(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t s
   using mf::kNoZ;
   using mf::kZDet;
   using mf::kZSweep;
+  constexpr int full = mf::kWithGammas | mf::kWithMoments;
   switch (id) {
-    case kPlaneFirst: launch_plane<R, N, false, kZSweep, true, true>(a, nch, st); return true;
-    case kPlaneMidFull: launch_plane<R, N, true, kZSweep, true, true>(a, nch, st); return true;
-    case kPlaneGamma: launch_plane<R, N, false, kZSweep, true, true>(a, nch, st, false, true); return true;
-    case kPlaneMid: launch_plane_mid<R, N, kZSweep>(a, nch, st); return true;
-    case kPlaneLast: launch_plane<R, N, true, kNoZ, false>(a, nch, st); return true;
-    case kPlaneZ: launch_plane<R, N, false, kZSweep, false, true>(a, nch, st); return true;
+    case kPlaneFirst: launch_plane<R, N, false, kZSweep, true, full>(a, nch, st); return true;
+    case kPlaneMid: launch_plane_sized<R, N, kZSweep>(a, nch, st); return true;
+    case kPlaneMidRec: launch_plane<R, N, true, kZSweep, true, mf::kWithMoments>(a, nch, st); return true;
+    case kPlaneMidFull: launch_plane<R, N, true, kZSweep, true, full>(a, nch, st); return true;
+    case kPlaneLast: launch_plane_sized<R, N, kNoZ, false>(a, nch, st); return true;
+    case kPlaneZ: launch_plane<R, N, false, kZSweep, false, full>(a, nch, st); return true;
     case kPlaneYF: launch_plane<R, N, false, kNoZ, true>(a, nch, st); return true;
-    case kPlaneDet: launch_plane_mid<R, N, kZDet>(a, nch, st); return true;
+    case kPlaneDet: launch_plane_sized<R, N, kZDet>(a, nch, st); return true;
     case kPlanePk: launch_plane<R, N, true, kNoZ, false>(a, nch, st, true); return true;
+    case kPlaneGamma: launch_plane<R, N, false, kZSweep, true, full>(a, nch, st, false, true); return true;
     case kColumn: launch_column<R, N, mf::kXSample>(a, nch, st); return true;
     case kColumnAhead:
       if constexpr (sizeof(R) == 8) launch_column<R, N, mf::kXSample, true>(a, nch, st);
@@ -650,8 +657,9 @@ void launch(int id, const mf::SweepArgs<R>& a, int n, int nch, hipStream_t st, b
 
 // path < 0: the problem's Gibbs-sweep path and tile variants; a given path
 // (the mixing sweep's split path, the plane path) runs x-tile variant 1.
+// gam_sweeps: sweeps of a launch with gamma variates.
 mf_status launch_checked(mf_problem* p, int id, int staging_chain, hipStream_t st, int path = -1,
-                         int pk_mode = mf::kPkDraw) {
+                         int pk_mode = mf::kPkDraw, int gam_sweeps = 1) {
   const int nch = p->desc.n_chains;
   const int xv = path < 0 ? p->xvar : 1, yv = p->yvar + 3 * p->yrad;
   if (path < 0) path = p->kernel_path();
@@ -662,12 +670,14 @@ mf_status launch_checked(mf_problem* p, int id, int staging_chain, hipStream_t s
     a.staging_chain = staging_chain;
     a.rev = rev;
     a.pk_mode = pk_mode;
+    a.gam_sweeps = gam_sweeps;
     launch<double>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
   } else {
     auto a = args_of<float>(p, path, xv);
     a.staging_chain = staging_chain;
     a.rev = rev;
     a.pk_mode = pk_mode;
+    a.gam_sweeps = gam_sweeps;
     launch<float>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
   }
   const hipError_t e = hipGetLastError();
@@ -717,21 +727,21 @@ mf_status launch_sweep_kernel(mf_problem* p, int k, hipStream_t st) {
                      : launch_checked(p, kSweepOrder[k], 0, st);
 }
 
-// The parts of a run of n sweeps: the first sweep, every further one, the end.
-// The plane path's gamma variates last kGammaAhead sweeps, so every
-// kGammaAhead-th sweep computes the next ones (full).
-enum RunPart : int { kRunFirst, kRunNext, kRunNextFull, kRunEnd };
+// The parts of a run of n sweeps: the first sweep, every further one (Rec: a
+// recorded one), the end.  The plane path's gamma variates last at most
+// kGammaAhead sweeps, so every kGammaAhead-th sweep computes the next ones (Full).
+enum RunPart : int { kRunFirst, kRunNext, kRunNextRec, kRunNextFull, kRunEnd };
 
-// Part of the i-th sweep of a run, whose index is `sweep`: one with recorded
-// moments takes the full plane kernel, too, and so does every sweep of a
-// problem whose index the host does not know (the kernel decides by the
-// device's).
+// Part of the i-th sweep of a run, whose index is `sweep`.  Any sweep of a
+// problem whose index the host does not know may be a recorded one (the kernel
+// decides by the device's index).
 RunPart run_part(const mf_problem* p, int i, uint64_t sweep) {
   if (i == 0) return kRunFirst;
+  if (i % static_cast<int>(mf::kGammaAhead) == 0) return kRunNextFull;
   const DiagRec& d = p->diag;
   const bool record = d.mom != nullptr &&
                       (p->captured || (sweep >= d.start && (sweep - d.start) % d.thin == 0));
-  return record || i % static_cast<int>(mf::kGammaAhead) == 0 ? kRunNextFull : kRunNext;
+  return record ? kRunNextRec : kRunNext;
 }
 
 // Whether the caller is capturing the stream (never the null stream, which
@@ -744,23 +754,26 @@ bool note_capture(mf_problem* p, hipStream_t st) {
   return on;
 }
 
-// more: another sweep of the run follows (its normals may be drawn now).  owed
-// (nullptr while capturing): what the field is owed after the launches made.
-mf_status launch_run_part(mf_problem* p, RunPart part, hipStream_t st, bool more = true,
+// left: sweeps of the run from this one on; the gamma variates that they need
+// are computed now, and the next one's normals may be.  owed (nullptr while
+// capturing): what the field is owed after the launches made.
+mf_status launch_run_part(mf_problem* p, RunPart part, hipStream_t st, int left,
                           mf_problem::Owed* owed = nullptr) {
   mf_status r = MF_OK;
   if (p->planes()) {
     auto step = [&](int id, mf_problem::Owed then) {
-      if (r == MF_OK) r = launch_checked(p, id, 0, st, kPathPlane);
+      if (r == MF_OK)
+        r = launch_checked(p, id, 0, st, kPathPlane, mf::kPkDraw,
+                           std::min(left, static_cast<int>(mf::kGammaAhead)));
       if (r == MF_OK && owed != nullptr) *owed = then;
     };
     if (part == kRunEnd) {
       step(kPlaneLast, mf_problem::kNothing);
       return r;
     }
-    step(part == kRunFirst ? kPlaneFirst : (part == kRunNext ? kPlaneMid : kPlaneMidFull),
-         mf_problem::kOwesColumn);
-    step(more && draws_ahead(p->desc) ? kColumnAhead : kColumn, mf_problem::kOwesEnd);
+    const int plane[kRunEnd] = {kPlaneFirst, kPlaneMid, kPlaneMidRec, kPlaneMidFull};
+    step(plane[part], mf_problem::kOwesColumn);
+    step(left > 1 && draws_ahead(p->desc) ? kColumnAhead : kColumn, mf_problem::kOwesEnd);
     return r;
   }
   for (int k = 0; k < MF_NUM_KERNELS && part != kRunEnd && r == MF_OK; ++k)
@@ -1068,11 +1081,11 @@ mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
   if (st != MF_OK) return st;
   mf_problem::Owed* owed = note_capture(p, hs) ? nullptr : &p->owed;
   for (int i = 0; i < n_sweeps; ++i) {
-    if ((st = launch_run_part(p, run_part(p, i, p->sweep), hs, i + 1 < n_sweeps, owed)) != MF_OK)
+    if ((st = launch_run_part(p, run_part(p, i, p->sweep), hs, n_sweeps - i, owed)) != MF_OK)
       return st;
     ++p->sweep;
   }
-  return n_sweeps > 0 ? launch_run_part(p, kRunEnd, hs, false, owed) : MF_OK;
+  return n_sweeps > 0 ? launch_run_part(p, kRunEnd, hs, 0, owed) : MF_OK;
 }
 
 mf_status mf_mixing_sweep(mf_problem* p, int32_t n_sweeps, void* stream) {
@@ -1562,7 +1575,7 @@ void mf_destroy_problem(mf_problem* p) { delete p; }
 // each of 48^3, 80^3 and 96^3 take 156 us a sweep joined every time, 136 every
 // 4 sweeps, 136 every 8.
 constexpr int kGraphSweeps = 4;
-constexpr int kGraphMany = 4, kGraphParts = 5;   // after the RunParts
+constexpr int kGraphMany = kRunEnd + 1, kGraphParts = kGraphMany + 1;   // after the RunParts
 
 struct mf_graph {
   std::vector<mf_problem*> probs;
@@ -1570,7 +1583,8 @@ struct mf_graph {
   std::vector<hipEvent_t> events;
   // one graph per part of a run (RunPart), and one of kGraphSweeps further
   // sweeps: the problems' branches join once in it, not after every sweep.
-  // Without a plane path every sweep is a first one, and there is no end.
+  // Without a plane path every sweep is a first one, and there is no end; the
+  // part of recorded sweeps is there if a problem records moments.
   hipGraph_t graph[kGraphParts] = {};
   hipGraphExec_t exec[kGraphParts] = {};
   std::vector<bool> planes;   // whether a problem's branch runs the two-pass sweep
@@ -1623,13 +1637,15 @@ mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, 
     return bail("hipStreamCreateWithFlags", e);
   g->side.push_back(cap);
   hs = cap;
-  bool any_planes = false;
+  bool any_planes = false, any_moments = false;
   for (int i = 0; i < n; ++i) {
+    any_moments |= problems[i]->diag.mom != nullptr;
     g->planes.push_back(problems[i]->planes());
     any_planes |= problems[i]->planes();
   }
   for (int part = kRunFirst; part < kGraphParts; ++part) {
     if (part != kRunFirst && part != kGraphMany && !any_planes) continue;
+    if (part == kRunNextRec && !any_moments) continue;
     if ((e = hipStreamBeginCapture(hs, hipStreamCaptureModeThreadLocal)) != hipSuccess)
       return bail("hipStreamBeginCapture", e);
     mf_status st = MF_OK;
@@ -1638,9 +1654,10 @@ mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, 
       if (part == kRunEnd && !problems[i]->planes()) continue;
       hipStream_t s2 = g->side[i];
       (void)hipStreamWaitEvent(s2, g->events[n], 0);
-      const RunPart one = part == kGraphMany ? kRunNext : static_cast<RunPart>(part);
+      RunPart one = part == kGraphMany ? kRunNext : static_cast<RunPart>(part);
+      if (one == kRunNextRec && problems[i]->diag.mom == nullptr) one = kRunNext;
       for (int k = 0; k < (part == kGraphMany ? kGraphSweeps : 1) && st == MF_OK; ++k)
-        st = launch_run_part(problems[i], one, s2);
+        st = launch_run_part(problems[i], one, s2, static_cast<int>(mf::kGammaAhead));
       (void)hipEventRecord(g->events[i], s2);
       (void)hipStreamWaitEvent(hs, g->events[i], 0);     // join
     }

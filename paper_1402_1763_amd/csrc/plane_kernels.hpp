@@ -241,6 +241,9 @@ __host__ __device__ __forceinline__ int coef_entry(int ix, int p, int n, int& ti
 }
 
 enum : int { kNoZ = -1 };   // ZMODE of a plane kernel without its z part
+// What a plane kernel does besides its plane: gamma variates of the P draws in
+// extra workgroups, the update of the recorded moments.
+enum : int { kWithGammas = 1, kWithMoments = 2 };
 
 // One (kz, iy) plane of one ix: the parts YI (inverse y-DFT), ZMODE (inverse
 // z-DFT, messenger step kZSweep or kZDet, forward z-DFT) and YF (forward
@@ -248,14 +251,16 @@ enum : int { kNoZ = -1 };   // ZMODE of a plane kernel without its z part
 // workgroups of a chain finish the P(k) step of the sweep before (pk_mode).
 //
 // The gamma variates of those steps take 116 registers and some 3 us of one
-// thread, but depend on the bin, the sweep and the chain alone.  Only the FULL
-// launches have them: a.gam_wgs more workgroups per chain compute those of this
-// sweep and the following ones, kGammaAhead in all, one per thread.  They also
-// have the update of the recorded moments; the launches between leave both out
-// and keep the registers of the transforms.
+// thread, but depend on the bin, the sweep and the chain alone.  Only the first
+// launch of a run and every kGammaAhead-th one have them (X & kWithGammas):
+// a.gam_wgs more workgroups per chain compute those of this sweep and the
+// following ones, a.gam_sweeps in all, one per thread.  Only launches of recorded
+// sweeps update the moments (X & kWithMoments); the others keep the registers
+// of the transforms.  us per recorded sweep with the gamma variates in all of
+// them : without, FP32, 16 chains of 48^3 39.9 : 29.3, 8 of 80^3 61.5 : 60.1.
 // With NORM the messenger's normals come from a.nrm, where the column kernel
 // before put them (column_kernel, AHEAD).
-template <typename R, int N, bool YI, int ZMODE, bool YF, bool FULL = false, bool MANY = false,
+template <typename R, int N, bool YI, int ZMODE, bool YF, int X = 0, bool MANY = false,
           bool NORM = false>
 __global__ void __launch_bounds__((PlaneTile<R, N, MANY>::NT), (PlaneTile<R, N, MANY>::WAVES))
 plane_kernel(SweepArgs<R> a) {
@@ -271,10 +276,10 @@ plane_kernel(SweepArgs<R> a) {
   Exchange<cx<R>, T::LDS, T::TWO> lds(field);
   const int tid = threadIdx.x, c = blockIdx.z;
   int ix = blockIdx.x;
-  if (FULL) {
+  if (X & kWithGammas) {
     if (ix < a.gam_wgs) {
       const uint32_t first = a.ctr[0];
-      for (int it = ix * NT + tid; it < static_cast<int>(kGammaAhead) * a.nb; it += a.gam_wgs * NT) {
+      for (int it = ix * NT + tid; it < a.gam_sweeps * a.nb; it += a.gam_wgs * NT) {
         const uint32_t n = first + it / a.nb;
         const int b = it % a.nb;
         a.gam[(static_cast<size_t>(n % kGammaSlots) * a.gam_chains + c) * a.nb + b] =
@@ -367,13 +372,13 @@ plane_kernel(SweepArgs<R> a) {
     // observed voxel in it; they are (1, 0) elsewhere, stored or not
     const uint32_t* obs = a.tile_obs + static_cast<size_t>(c) * a.ztiles;
     const R* coef = a.coef + static_cast<size_t>(c) * 2 * a.m;
-    const int rec = FULL && ZMODE == kZSweep && a.mom != nullptr ? recorded(a, sweep) : -1;
+    const int rec = (X & kWithMoments) && ZMODE == kZSweep && a.mom != nullptr ? recorded(a, sweep) : -1;
 #pragma unroll
     for (int i = 0; i < Z::slots(RL); ++i) {
       int p = 0, q = 0;
       if (!Z::template at<RL>(i, p, q)) continue;
       cx<R>* s = v + i * RL;
-      if (FULL && rec >= 0) {   // Welford update with the (rec + 1)-th sample
+      if ((X & kWithMoments) && rec >= 0) {   // Welford update with the (rec + 1)-th sample
         const double inv_k = 1.0 / (rec + 1.0);
         double* mean = a.mom + static_cast<size_t>(c) * 2 * a.m;
         double* m2 = mean + a.m;

@@ -85,7 +85,8 @@ struct SweepArgs {
   // (they do not depend on the field); sweep n's at slot n mod kGammaSlots.
   double* gam;            // [kGammaSlots][chain][nb]
   int32_t gam_chains;     // chains of the problem (slot stride / nb)
-  int32_t gam_wgs;        // workgroups per chain of this launch that compute kGammaAhead sweeps
+  int32_t gam_sweeps;     // sweeps whose variates this launch computes, at most kGammaAhead
+  int32_t gam_wgs;        // its workgroups per chain that do so
   // Plane path with CUs to spare: the next sweep's messenger normals, in the
   // order of the coefficients (a voxel pair's two per entry); else nullptr.
   cx<R>* nrm;             // [chain][m / 2]

@@ -188,3 +188,28 @@ def test_a_path_chosen_is_the_path_run_timed_and_reported(run):
             assert sum(k == f"xsplit_kernel<float, 64, 0, {v}>" for k in runs) >= 18, v
         assert sum(k.startswith("column") for k in runs) == 3 * 6
     """)
+
+
+def test_gamma_variates_are_computed_for_the_sweeps_that_use_them(run):
+    """The workgroups of a run's first launch: the planes and as many more as the
+    gamma variates of the run's sweeps take, at most 32 of them; recorded sweeps
+    compute none, and every 32nd sweep those of the next."""
+    run("""
+        nb, nt = 300, 256                    # threads of a 64^3 FP32 plane
+        wgs = lambda sweeps: -(-sweeps * nb // nt)
+        def first(h, n):
+            sweep(h, n)
+            return [int(l.split(" grid ")[1].split()[0]) for l in log() if l.startswith("plane")]
+        h = problem(64, nb=nb)
+        for n in (1, 3, 32, 33, 40):
+            assert first(h, n)[0] == 64 + wgs(min(n, 32)), n
+        grids = first(h, 70)
+        assert grids[32] == 64 + nb + wgs(32) and grids[64] == 64 + nb + wgs(6)
+        assert set(grids[1:32] + grids[33:64] + grids[65:]) == {64 + nb}
+        mom = np.zeros(2 * 64 ** 3)
+        assert lib.mf_set_diagnostics(ctypes.c_void_p(h), ctypes.c_uint64(0), 1, None, 0,
+                                      ctypes.c_void_p(mom.ctypes.data), None) == 0
+        log()
+        assert first(h, 20)[1:] == [64 + nb] * 20
+        assert first(problem(64, nb=nb, sample_pk=False), 3) == [64, 64 + nb, 64 + nb, 64 + nb]
+    """)
