@@ -296,7 +296,8 @@ plane_kernel(SweepArgs<R> a) {
       pk_draw_block<R, NT, true>(a, ix, c, reinterpret_cast<double*>(field), ZP ? a.ctr[0] - 1u : a.ctr[1]);
       return;
     }
-    ix -= a.nb;
+    ix -= pk_blocks(a.nb);
+    if (ix < 0) return;
   }
   const cx<R>* src = a.spec_in + static_cast<size_t>(c) * a.spec_stride + static_cast<size_t>(ix) * N;
   cx<R>* dst = a.spec + static_cast<size_t>(c) * a.spec_stride + static_cast<size_t>(ix) * N;

@@ -720,8 +720,8 @@ __device__ __forceinline__ void plane_block(int lin, int per_plane, bool rev, in
   }
 }
 
-// Workgroups ahead of the inverse y-pass's planes: the nb of the P(k) step, up
-// to a multiple of 8 so that the planes keep their XCDs.
+// Workgroups of the P(k) step ahead of the planes of the inverse y-pass and of
+// the plane kernel: nb, up to a multiple of 8 so that the planes keep their XCDs.
 __host__ __device__ constexpr int pk_blocks(int nb) { return (nb + 7) / 8 * 8; }
 
 // Forward y-pass with x stage A (INV = false), or inverse x stage A with the

@@ -193,14 +193,16 @@ def test_a_path_chosen_is_the_path_run_timed_and_reported(run):
 def test_gamma_variates_are_computed_for_the_sweeps_that_use_them(run):
     """The workgroups of a run's first launch: the planes and as many more as the
     gamma variates of the run's sweeps take, at most 32 of them; recorded sweeps
-    compute none, and every 32nd sweep those of the next."""
+    compute none, and every 32nd sweep those of the next.  The workgroups ahead of
+    the planes (these, and one per bin of the P draw) come in eights."""
     run("""
-        nb, nt = 300, 256                    # threads of a 64^3 FP32 plane
-        wgs = lambda sweeps: -(-sweeps * nb // nt)
+        bins, nt = 300, 256                  # threads of a 64^3 FP32 plane
+        wgs = lambda sweeps: -(-sweeps * bins // (8 * nt)) * 8
+        nb = 304
         def first(h, n):
             sweep(h, n)
             return [int(l.split(" grid ")[1].split()[0]) for l in log() if l.startswith("plane")]
-        h = problem(64, nb=nb)
+        h = problem(64, nb=bins)
         for n in (1, 3, 32, 33, 40):
             assert first(h, n)[0] == 64 + wgs(min(n, 32)), n
         grids = first(h, 70)
@@ -211,5 +213,5 @@ def test_gamma_variates_are_computed_for_the_sweeps_that_use_them(run):
                                       ctypes.c_void_p(mom.ctypes.data), None) == 0
         log()
         assert first(h, 20)[1:] == [64 + nb] * 20
-        assert first(problem(64, nb=nb, sample_pk=False), 3) == [64, 64 + nb, 64 + nb, 64 + nb]
+        assert first(problem(64, nb=bins, sample_pk=False), 3) == [64, 64 + nb, 64 + nb, 64 + nb]
     """)
