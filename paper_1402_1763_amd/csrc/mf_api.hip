@@ -502,7 +502,7 @@ void launch_ysplit(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   using YS = mf::YSTile<R, N, V>;
   const int extra = INV ? mf::pk_blocks(a.nb) : 0;   // the P(k) workgroups
   hipLaunchKernelGGL((mf::ysplit_kernel<R, N, INV, V, RV>),
-                     dim3(16 / YS::G * (N / 2 + 1) + extra, 1, nch), dim3(YS::NT), 0, st, a);
+                     dim3(mf::plane_blocks(N, 16 / YS::G) + extra, 1, nch), dim3(YS::NT), 0, st, a);
 }
 
 // The split y-pass of y variant yv: units variant yv % 3 (G, G/2, G/4), radix
@@ -524,7 +524,7 @@ template <typename R, int N, int V>
 void launch_xsplit(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   using XS = mf::XSTile<R, N, V>;
   const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
-  hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXSample, V>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
+  hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXSample, V>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch),
                      dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
 }
 
@@ -537,7 +537,7 @@ template <typename R, int N, int V>
 void launch_xmix(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
   using XS = mf::XSTile<R, N, V>;
   const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
-  hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXMix, V>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
+  hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXMix, V>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch),
                      dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 2) * sizeof(double) + tables, st, a);
 }
 
@@ -600,7 +600,7 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
       break;
     case kXDetK:
       if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXDet, 1>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
+        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXDet, 1>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch),
                            dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
       break;
     case kXMixK:
@@ -611,7 +611,7 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
       break;
     case kXMixInvK:
       if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xmixinv_kernel<R, N>), dim3(XS::WPP * (N / 2 + 1), 1, nch), dim3(XS::NT),
+        hipLaunchKernelGGL((mf::xmixinv_kernel<R, N>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch), dim3(XS::NT),
                            a.nb * sizeof(R) + (a.nb + 1) * 4, st, a);
       break;
     case kMixPkK:
@@ -619,7 +619,7 @@ void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool w
       break;
     case kXAdjK:
       if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXAdj, 1>), dim3(XS::WPP * (N / 2 + 1), 1, nch),
+        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXAdj, 1>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch),
                            dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
       break;
     case kX:

@@ -215,3 +215,20 @@ def test_gamma_variates_are_computed_for_the_sweeps_that_use_them(run):
         assert first(h, 20)[1:] == [64 + nb] * 20
         assert first(problem(64, nb=bins, sample_pk=False), 3) == [64, 64 + nb, 64 + nb, 64 + nb]
     """)
+
+
+def test_every_chain_starts_on_the_same_xcd(run):
+    """Workgroups of the passes over planes come in eights per chain."""
+    run("""
+        for n, precision, nb in ((48, "fp32", 5), (80, "fp64", 9), (96, "fp64", 16), (128, "fp32", 33)):
+            h = problem(n, precision, 3, nb)
+            assert lib.mf_set_tuning(ctypes.c_void_p(h), ctypes.byref(binding.mf_tuning(x_path=0))) == 0
+            sweep(h, 1)
+            assert lib.mf_mixing_sweep(ctypes.c_void_p(h), 1, None) == 0
+            assert lib.mf_set_tuning(ctypes.c_void_p(h), ctypes.byref(binding.mf_tuning(x_path=1))) == 0
+            sweep(h, 3)
+            for line in log():
+                kernel, grid = line.split(" grid ")
+                if kernel.startswith(("ysplit", "xsplit", "xmixinv", "plane")):
+                    assert int(grid.split()[0]) % 8 == 0, line
+    """)
