@@ -321,18 +321,23 @@ mf_status mf_debug_spectrum(mf_problem* p, int32_t chain, double* buf, int32_t t
 
 /* Graphs of sweeps, for batches of problems (different grid sizes or
  * precisions) run as independent chains (Sec. 3.4: independent chains need no
- * communication).  mf_graph_create captures Gibbs sweeps of each of the n
- * problems into HIP graphs (one sweep, and several at a time); problems are
- * independent branches of a graph and may run concurrently.  mf_graph_launch
- * replays n_sweeps sweeps on `stream` (asynchronously) and advances every problem's sweep counter; the
- * replays draw the same random numbers as mf_gibbs_sweep would.  The problems
+ * communication).  mf_graph_create captures four Gibbs sweeps of each of the n
+ * problems into a HIP graph; problems are independent branches of it and may run
+ * concurrently.  mf_graph_launch runs n_sweeps sweeps on `stream`
+ * (asynchronously) and advances every problem's sweep counter.  It replays
+ * graphs (further ones, of the beginning and the end of a run and of fewer sweeps, are
+ * captured at the first launch that uses them) and launches the sweeps that no
+ * graph holds, in branches on the graph's side streams joined with `stream`;
+ * they draw the same random numbers as mf_gibbs_sweep would.  `stream` must
+ * not be in capture (MF_E_DEVICE).  The problems
  * must outlive the graph and must not be swept on another stream while a
  * replay is in flight.  A graph replays the diagnostic recording set when it
  * was created (mf_set_diagnostics), buffers included, so that call is refused
  * for a problem while a graph over it exists.  It also keeps the x path and
  * tile variants chosen when it was created: a later mf_set_tuning or
  * mf_autotune changes eager sweeps only (every choice gives the same chain
- * up to rounding).  The graph owns its side streams and events.
+ * up to rounding).  The graph owns its side streams and events;
+ * mf_graph_destroy waits for what was launched on them.
  * Errors: MF_E_INVALID_ARG, MF_E_DEVICE. */
 typedef struct mf_graph mf_graph;
 mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, mf_graph** out);

@@ -318,6 +318,9 @@ struct mf_problem {
   int xpath;                    // XPath of Gibbs sweeps
   int xvar = 0, yvar = 0;       // split-path tile variants of Gibbs sweeps (autotuner)
   int yrad = 0;                 // 1: the split y-passes run their radix stages reversed
+  struct Choice { int xpath, xvar, yvar, yrad; };
+  Choice choice() const { return {xpath, xvar, yvar, yrad}; }
+  void choose(const Choice& c) { xpath = c.xpath, xvar = c.xvar, yvar = c.yvar, yrad = c.yrad; }
   int graphs = 0;               // live graphs that captured this problem's sweep
   // Sweeps of this problem were captured by its caller: replays move the device's
   // sweep index without the host's, which then says nothing about the next sweep.
@@ -1575,36 +1578,101 @@ void mf_destroy_problem(mf_problem* p) { delete p; }
 
 }  // extern "C"
 
-// Sweeps per graph of further sweeps.  Joining the branches after every sweep
-// leaves the device to the slowest of them each time: 32 chains of 64^3 and 8
-// each of 48^3, 80^3 and 96^3 take 156 us a sweep joined every time, 136 every
-// 4 sweeps, 136 every 8.
+// Sweeps per replay.  Joining the problems' branches after every sweep leaves the
+// device to the slowest of them each time: 32 chains of 64^3 and 8 each of 48^3,
+// 80^3 and 96^3 take 156 us a sweep joined every time, 136 every 4 sweeps, 136
+// every 8.
 constexpr int kGraphSweeps = 4;
-constexpr int kGraphMany = kRunEnd + 1, kGraphParts = kGraphMany + 1;   // after the RunParts
 
+// A graph holds a piece of a run: its first sweep or not, up to kGraphSweeps
+// plain further ones, its end or not.  The piece of kGraphSweeps further sweeps is
+// made with the mf_graph, the others at the first launch that needs them: a graph
+// of four branches takes 0.3 ms to make, the next ones up to 0.7 each.  Sweeps
+// that compute gamma variates or record moments are launched, in branches on the
+// side streams, and so is all but kGraphSweeps further sweeps of a single
+// problem, which needs no branches (one chain of 64^3, a sweep at a time: 16.8
+// us launched, 20.0 replayed).
 struct mf_graph {
   std::vector<mf_problem*> probs;
-  std::vector<hipStream_t> side;
-  std::vector<hipEvent_t> events;
-  // one graph per part of a run (RunPart), and one of kGraphSweeps further
-  // sweeps: the problems' branches join once in it, not after every sweep.
-  // Without a plane path every sweep is a first one, and there is no end; the
-  // part of recorded sweeps is there if a problem records moments.
-  hipGraph_t graph[kGraphParts] = {};
-  hipGraphExec_t exec[kGraphParts] = {};
-  std::vector<bool> planes;   // whether a problem's branch runs the two-pass sweep
+  std::vector<mf_problem::Choice> choice;   // the paths and tiles at its making
+  std::vector<hipStream_t> side;            // one per problem, and one to capture on
+  std::vector<hipEvent_t> events;           // one per problem, and one for the fork
+  hipGraph_t graph[2][kGraphSweeps + 1][2] = {};   // [with the first sweep][further sweeps][with the end]
+  hipGraphExec_t exec[2][kGraphSweeps + 1][2] = {};
   bool counted = false;   // probs' graph counts include this graph
+
+  // Forks a branch per problem off `st`, launches, and joins them; a single
+  // problem's launches stay on `st`.  launch(stream_of) -> mf_status, with
+  // stream_of(k) the stream of problem k.
+  template <class F>
+  mf_status branches(hipStream_t st, F launch) {
+    const size_t n = probs.size();
+    if (n == 1) return launch([&](size_t) { return st; });
+    MF_HIP(hipEventRecord(events[n], st));
+    for (size_t k = 0; k < n; ++k) MF_HIP(hipStreamWaitEvent(side[k], events[n], 0));
+    const mf_status r = launch([&](size_t k) { return side[k]; });
+    for (size_t k = 0; k < n; ++k) {   // joined after a failure, too
+      MF_HIP(hipEventRecord(events[k], side[k]));
+      MF_HIP(hipStreamWaitEvent(st, events[k], 0));
+    }
+    return r;
+  }
   ~mf_graph() {
     if (counted)
       for (auto* p : probs) --p->graphs;
-    for (auto e : exec)
-      if (e) (void)hipGraphExecDestroy(e);
-    for (auto g : graph)
-      if (g) (void)hipGraphDestroy(g);
+    for (int k = 0; k < 4 * (kGraphSweeps + 1); ++k) {
+      if ((&exec[0][0][0])[k]) (void)hipGraphExecDestroy((&exec[0][0][0])[k]);
+      if ((&graph[0][0][0])[k]) (void)hipGraphDestroy((&graph[0][0][0])[k]);
+    }
     for (auto e : events) (void)hipEventDestroy(e);
-    for (auto s : side) (void)hipStreamDestroy(s);
+    for (auto s : side) {   // the sweeps launched on them may still run
+      (void)hipStreamSynchronize(s);
+      (void)hipStreamDestroy(s);
+    }
   }
 };
+
+namespace {
+
+// Makes the graph of a piece of a run, with the problems' present choices, if it
+// is not there.  Captured on a stream of the graph's own (the caller's may be the
+// legacy default stream, which cannot be captured); replays go to the caller's.
+mf_status make_piece(mf_graph* g, bool first, int further, bool end) {
+  hipGraphExec_t& exec = g->exec[first][further][end];
+  if (exec != nullptr) return MF_OK;
+  hipStream_t cap = g->side.back();
+  MF_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
+  const mf_status st = g->branches(cap, [&](auto stream_of) {
+    mf_status r = MF_OK;
+    for (int i = first ? 0 : 1; i <= further + (end ? 1 : 0); ++i)
+      for (size_t k = 0; k < g->probs.size() && r == MF_OK; ++k) {
+        const RunPart part = i > further ? kRunEnd : (i == 0 ? kRunFirst : kRunNext);
+        r = launch_run_part(g->probs[k], part, stream_of(k),
+                            end ? 1 + further - i : static_cast<int>(mf::kGammaAhead));
+      }
+    return r;
+  });
+  hipGraph_t& graph = g->graph[first][further][end];
+  const hipError_t e = hipStreamEndCapture(cap, &graph);
+  if (st != MF_OK) return st;
+  MF_HIP(e);
+  MF_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+  return MF_OK;
+}
+
+// Replays a piece of a run and counts its sweeps.
+mf_status launch_piece(mf_graph* g, bool first, int further, bool end, hipStream_t st) {
+  const mf_status r = make_piece(g, first, further, end);
+  if (r != MF_OK) return r;
+  MF_HIP(hipGraphLaunch(g->exec[first][further][end], st));
+  for (auto* p : g->probs) {
+    p->sweep += static_cast<uint64_t>(further + (first ? 1 : 0));
+    if (p->planes()) p->owed = end ? mf_problem::kNothing : mf_problem::kOwesEnd;
+  }
+  return MF_OK;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -1614,7 +1682,7 @@ mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, 
   if (!problems || n < 1) return fail(MF_E_INVALID_ARG, "need at least one problem");
   for (int i = 0; i < n; ++i)
     if (!problems[i]) return fail(MF_E_INVALID_ARG, "problem %d is NULL", i);
-  hipStream_t hs = static_cast<hipStream_t>(stream);
+  (void)stream;   // the capture has a stream of its own
   mf_graph* g = new mf_graph{};
   g->probs.assign(problems, problems + n);
   auto bail = [&](const char* what, hipError_t e) {
@@ -1634,46 +1702,15 @@ mf_status mf_graph_create(mf_problem* const* problems, int32_t n, void* stream, 
       return bail("hipEventCreate", e);
     g->events.push_back(ev);
   }
-  // Capture on a stream of the graph's own (the caller's may be the legacy
-  // default stream, which cannot be captured); replays go to the caller's.
-  (void)hs;
   hipStream_t cap;
   if ((e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking)) != hipSuccess)
     return bail("hipStreamCreateWithFlags", e);
   g->side.push_back(cap);
-  hs = cap;
-  bool any_planes = false, any_moments = false;
-  for (int i = 0; i < n; ++i) {
-    any_moments |= problems[i]->diag.mom != nullptr;
-    g->planes.push_back(problems[i]->planes());
-    any_planes |= problems[i]->planes();
-  }
-  for (int part = kRunFirst; part < kGraphParts; ++part) {
-    if (part != kRunFirst && part != kGraphMany && !any_planes) continue;
-    if (part == kRunNextRec && !any_moments) continue;
-    if ((e = hipStreamBeginCapture(hs, hipStreamCaptureModeThreadLocal)) != hipSuccess)
-      return bail("hipStreamBeginCapture", e);
-    mf_status st = MF_OK;
-    (void)hipEventRecord(g->events[n], hs);             // fork point
-    for (int i = 0; i < n && st == MF_OK; ++i) {
-      if (part == kRunEnd && !problems[i]->planes()) continue;
-      hipStream_t s2 = g->side[i];
-      (void)hipStreamWaitEvent(s2, g->events[n], 0);
-      RunPart one = part == kGraphMany ? kRunNext : static_cast<RunPart>(part);
-      if (one == kRunNextRec && problems[i]->diag.mom == nullptr) one = kRunNext;
-      for (int k = 0; k < (part == kGraphMany ? kGraphSweeps : 1) && st == MF_OK; ++k)
-        st = launch_run_part(problems[i], one, s2, static_cast<int>(mf::kGammaAhead));
-      (void)hipEventRecord(g->events[i], s2);
-      (void)hipStreamWaitEvent(hs, g->events[i], 0);     // join
-    }
-    e = hipStreamEndCapture(hs, &g->graph[part]);
-    if (st != MF_OK) {
-      delete g;
-      return st;
-    }
-    if (e != hipSuccess) return bail("hipStreamEndCapture", e);
-    if ((e = hipGraphInstantiate(&g->exec[part], g->graph[part], nullptr, nullptr, 0)) != hipSuccess)
-      return bail("hipGraphInstantiate", e);
+  for (auto* p : g->probs) g->choice.push_back(p->choice());
+  const mf_status st = make_piece(g, false, kGraphSweeps, false);
+  if (st != MF_OK) {
+    delete g;
+    return st;
   }
   // the graph holds the diagnostic buffers' addresses as captured
   for (auto* p : g->probs) ++p->graphs;
@@ -1691,29 +1728,60 @@ mf_status mf_graph_launch(mf_graph* g, int32_t n_sweeps, void* stream) {
     if (room == MF_OK) room = check_sweep_room(p, n_sweeps);
     if (room != MF_OK) return room;
   }
-  const bool planes = g->exec[kRunEnd] != nullptr;
-  auto part_of = [&](int i) {   // the fullest that a problem's i-th sweep needs
-    int part = planes ? kRunFirst : kRunNext;
-    if (planes)
-      for (auto* p : g->probs) part = std::max<int>(part, run_part(p, i, p->sweep + i));
-    return part;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hs != nullptr && hipStreamIsCapturing(hs, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+    return fail(MF_E_DEVICE, "a graph cannot be launched into a stream that is being captured");
+  // the launches made here follow the choices that the graph was made with
+  const size_t n = g->probs.size();
+  std::vector<mf_problem::Choice> later;
+  for (size_t k = 0; k < n; ++k) {
+    later.push_back(g->probs[k]->choice());
+    g->probs[k]->choose(g->choice[k]);
+  }
+  bool planes = false;   // else a run's first sweep is as any other, and it has no end
+  for (auto* p : g->probs) planes |= p->planes();
+  int i = 0;             // sweeps done
+  // plain further sweeps from the from-th on, at most `most`
+  auto plain = [&](int from, int most) {
+    for (int count = 0; count < most && from + count < n_sweeps; ++count)
+      for (auto* p : g->probs)
+        if (p->planes() && run_part(p, from + count, p->sweep + (from + count - i)) != kRunNext) return count;
+    return std::min(most, n_sweeps - from);
   };
-  hipError_t e = hipSuccess;
-  int i = 0;
-  while (i < n_sweeps && e == hipSuccess) {
-    int same = 0;   // plain further sweeps from here on
-    while (same < kGraphSweeps && i + same < n_sweeps && part_of(i + same) == kRunNext) ++same;
-    const bool many = same == kGraphSweeps;
-    e = hipGraphLaunch(g->exec[many ? kGraphMany : (planes ? part_of(i) : kRunFirst)], hs);
-    if (e == hipSuccess) i += many ? kGraphSweeps : 1;
+  mf_status st = MF_OK;
+  while (i < n_sweeps && st == MF_OK) {
+    // the next piece; a run's first sweep takes the odd further ones along, so
+    // that pieces of kGraphSweeps make up the rest
+    const int first = planes && i == 0 ? 1 : 0;
+    int further = plain(i + first, static_cast<int>(mf::kGammaAhead));
+    if (first && further >= kGraphSweeps) further %= kGraphSweeps;
+    further = std::min(further, kGraphSweeps);
+    if (n > 1 ? first + further > 0 : !first && further == kGraphSweeps) {
+      const bool end = planes && n > 1 && i + first + further == n_sweeps;
+      st = launch_piece(g, first != 0, further, end, hs);
+      if (st == MF_OK) i += first + further;
+      if (i < n_sweeps || end || !planes) continue;
+    }
+    // what is launched: sweeps up to the next piece, and the run's end
+    if (st == MF_OK) st = g->branches(hs, [&](auto stream_of) {
+      mf_status r = MF_OK;
+      while (i < n_sweeps && r == MF_OK) {
+        for (size_t k = 0; k < n && r == MF_OK; ++k) {
+          mf_problem* p = g->probs[k];
+          r = launch_run_part(p, run_part(p, i, p->sweep), stream_of(k), n_sweeps - i, &p->owed);
+          if (r == MF_OK) ++p->sweep;
+        }
+        ++i;
+        const int enough = n > 1 ? 1 : kGraphSweeps;
+        if (plain(i, enough) == enough) break;
+      }
+      for (size_t k = 0; i == n_sweeps && k < n && r == MF_OK; ++k)
+        r = launch_run_part(g->probs[k], kRunEnd, stream_of(k), 0, &g->probs[k]->owed);
+      return r;
+    });
   }
-  if (n_sweeps > 0 && e == hipSuccess && planes) e = hipGraphLaunch(g->exec[kRunEnd], hs);
-  for (size_t k = 0; k < g->probs.size(); ++k) {
-    g->probs[k]->sweep += static_cast<uint64_t>(i);
-    if (e != hipSuccess && i > 0 && g->planes[k]) g->probs[k]->owed = mf_problem::kOwesEnd;
-  }
-  MF_HIP(e);
-  return MF_OK;
+  for (size_t k = 0; k < n; ++k) g->probs[k]->choose(later[k]);
+  return st;
 }
 
 void mf_graph_destroy(mf_graph* g) { delete g; }

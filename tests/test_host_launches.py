@@ -123,16 +123,75 @@ def test_every_call_on_the_field_completes_a_run_first(run):
 
 
 def test_a_graph_launch_that_fails_counts_and_completes_its_sweeps(run):
+    """The failing step of a launch of 10 sweeps: the first sweep's launches,
+    replays of four, the sweep left over or the end."""
     run("""
+        end = "plane_kernel<float, 64, true, -1, false"
+        for nth in range(7):
+            h = problem(64)
+            g = binding.mf_graph_create([h], 0)
+            log()
+            stub.stub_fail_launch(nth)
+            assert lib.mf_graph_launch(ctypes.c_void_p(g), 10, None) == binding.MF_E_DEVICE
+            ran = sum("column" in l for l in log())
+            assert ran == (0, 0, 1, 5, 9, 9, 10)[nth]
+            assert state(h) == 0
+            owed = names(log())[:-1]
+            half = nth in (1, 5)                     # a column owed
+            assert [k.startswith(end) for k in owed] == [False] * half + [True] * (nth > 0), (nth, owed)
+            assert binding.mf_get_chain_state(h, 0, 64, 8, 0, False)[2] == ran + half
+    """)
+
+
+def test_what_a_graph_launch_replays_and_launches(run):
+    """Several problems: pieces of a run are replayed, up to four further sweeps
+    each, and sweeps that renew the gamma variates launched.  A single problem:
+    four further sweeps are replayed, the others launched.  Every sweep is there
+    once, on the path of the graph's making."""
+    run("""
+        def launch(g, n, of):
+            binding.mf_graph_launch(g, n, 0)
+            lines = log()
+            assert sum("column" in l for l in lines) == of * n, (n, lines)
+            assert sum(", true, -1, false" in l for l in lines) == of, (n, lines)       # the end
+            assert sum("plane_kernel" in l and ", false, 0, true" in l for l in lines) == of    # the first sweep
+            return "".join("g" if l == "graph" else l[0] for l in lines if l[0] != " ")
+        a, b = problem(64), problem(48, chains=2)
+        g = binding.mf_graph_create([a, b], 0)
+        assert log() == []
+        both = "pcpc"                                      # a sweep of both
+        for n, want in ((1, "g"), (2, "g"), (4, "g"), (5, "gg"), (6, "gg"), (25, "g" * 7), (32, "g" * 8),
+                        (33, "g" * 8 + both + "pp"), (40, "g" * 8 + both + "gg"), (1, "g")):
+            assert launch(g, n, 2) == want, n
+        assert lib.mf_set_x_path(ctypes.c_void_p(a), 0) == 0
+        assert launch(g, 1, 2) == "g" and launch(g, 33, 2) == "g" * 8 + both + "pp"
+        path = ctypes.c_int32(-1)
+        lib.mf_get_x_path(ctypes.c_void_p(a), ctypes.byref(path))
+        assert path.value == 0
+        stub.stub_caller_captures(1)
+        assert lib.mf_graph_launch(ctypes.c_void_p(g), 1, ctypes.c_void_p(8)) == binding.MF_E_DEVICE and log() == []
+        stub.stub_caller_captures(0)
         h = problem(64)
         g = binding.mf_graph_create([h], 0)
+        for n, want in ((1, "pcp"), (4, "pc" * 4 + "p"), (5, "pcgp"), (10, "pcggpcp"),
+                        (40, "pc" + "g" * 7 + "pc" * 4 + "g" + "pc" * 3 + "p")):
+            assert launch(g, n, 1) == want, n
+        # moments of every fifth sweep: launched
+        mom = np.zeros(2 * 64 ** 3)
+        h, other = problem(64), problem(64)
+        assert lib.mf_set_diagnostics(ctypes.c_void_p(h), ctypes.c_uint64(0), 5, None, 0,
+                                      ctypes.c_void_p(mom.ctypes.data), None) == 0
         log()
-        stub.stub_fail_launch(2)                     # the third replay
-        assert lib.mf_graph_launch(ctypes.c_void_p(g), 6, None) == binding.MF_E_DEVICE
-        ran = sum(" " == l[0] and "column" in l for l in log())
-        assert ran > 0
-        assert state(h) == 0 and log()[0].startswith("plane_kernel<float, 64, true, -1, false")
-        assert binding.mf_get_chain_state(h, 0, 64, 8, 0, False)[2] == ran
+        g = binding.mf_graph_create([h, other], 0)
+        assert launch(g, 11, 2) == "gg" + both + "g" + both + "pp"
+        # without the two-pass sweep there is no first sweep and no end
+        h, other = problem(96, "fp64", 3), problem(64)
+        assert lib.mf_set_x_path(ctypes.c_void_p(other), 0) == 0
+        g = binding.mf_graph_create([h, other], 0)
+        for n, graphs in ((1, 1), (4, 1), (7, 2), (40, 10)):
+            binding.mf_graph_launch(g, n, 0)
+            lines = log()
+            assert lines.count("graph") == graphs and len(lines) == graphs + 8 * n
     """)
 
 
