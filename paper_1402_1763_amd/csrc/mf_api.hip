@@ -2473,6 +2473,11 @@ mf_status mf_acf(const double* trace, int32_t t, int32_t n_bins, int32_t max_lag
   if (t < 2 || n_bins < 1 || max_lag < 0 || max_lag >= t)
     return fail(MF_E_INVALID_ARG, "need t >= 2, n_bins >= 1 and 0 <= max_lag < t");
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  if (t <= mf::kAcfShort) {
+    hipLaunchKernelGGL(mf::acf_short_kernel, dim3(n_bins), dim3(mf::kAcfShortThreads), 0, hs, trace, t, n_bins,
+                       max_lag, acf, nc);
+    return check_launch("acf");
+  }
   const int64_t items = static_cast<int64_t>((n_bins - 1) / mf::kAcfBins + 1) * (max_lag / mf::kAcfLags + 1);
   const unsigned grid = static_cast<unsigned>(std::min<int64_t>(items, 1 << 20));
   hipLaunchKernelGGL(mf::acf_kernel, dim3(grid), dim3(mf::kAcfThreads), 0, hs, trace, t, n_bins,

@@ -352,10 +352,8 @@ acf_kernel(const double* trace, int t, int nb, int max_lag, int64_t items, doubl
   }
 }
 
-// nc[b] = the first lag with acf < 0.1, -1 if none: one wave per bin.
-__global__ void __launch_bounds__(64)
-acf_length_kernel(const double* acf, int nb, int max_lag, int32_t* nc) {
-  const int b = blockIdx.x, lane = threadIdx.x;
+// First lag with acf < 0.1 of bin b, -1 if none, by one wave.
+__device__ __forceinline__ void acf_length(const double* acf, int nb, int max_lag, int b, int lane, int32_t* nc) {
   for (int n0 = 0; n0 <= max_lag; n0 += 64) {
     const int n = n0 + lane;
     const bool low = n <= max_lag && acf[static_cast<size_t>(n) * nb + b] < 0.1;
@@ -366,6 +364,48 @@ acf_length_kernel(const double* acf, int nb, int max_lag, int32_t* nc) {
     }
   }
   if (lane == 0) nc[b] = -1;
+}
+
+// Short series: one workgroup per bin holds all of it in LDS, takes a lag per
+// thread in turn and finds the length in the same launch.  Tiles would be mostly
+// empty, and each workgroup of them takes some 7 us.  A call, tiles : this, 50
+// samples of 5 bins and 10 lags 14.7 : 11.4 us, 100 of 200 and 99 lags 26.2 :
+// 11.5, 300 of 8 and 15 lags 15.2 : 12.8; but 384 of 16 and 30 lags 14.8 : 15.4.
+constexpr int kAcfShort = 320, kAcfShortThreads = kWienerThreads;
+
+__global__ void __launch_bounds__(kAcfShortThreads)
+acf_short_kernel(const double* trace, int t, int nb, int max_lag, double* acf, int32_t* nc) {
+  __shared__ double x[kAcfShort + 8], red[kAcfShortThreads], sums[kAcfShort];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const double x0 = trace[b];   // the mean counted from it, as in acf_kernel
+  double s = 0.0;
+  for (int i = tid; i < t + 8; i += kAcfShortThreads) {
+    x[i] = i < t ? trace[static_cast<size_t>(i) * nb + b] : 0.0;
+    if (i < t) s += x[i] - x0;
+  }
+  const double mu = x0 + block_sum(red, s) / t;
+  __syncthreads();
+  for (int i = tid; i < t; i += kAcfShortThreads) x[i] -= mu;
+  __syncthreads();
+  for (int n = tid; n <= max_lag; n += kAcfShortThreads) {
+    double acc[8] = {0.0};
+    for (int i = 0; i < t - n; i += 8)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] += x[i + k] * (i + k < t - n ? x[i + k + n] : 0.0);
+    sums[n] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  }
+  __syncthreads();
+  const double var = sums[0] / t;
+  for (int n = tid; n <= max_lag; n += kAcfShortThreads)
+    acf[static_cast<size_t>(n) * nb + b] = sums[n] / ((t - n) * var);
+  __syncthreads();
+  if (tid < 64) acf_length(acf, nb, max_lag, b, tid, nc);
+}
+
+// The lengths after acf_kernel: one wave per bin.
+__global__ void __launch_bounds__(64)
+acf_length_kernel(const double* acf, int nb, int max_lag, int32_t* nc) {
+  acf_length(acf, nb, max_lag, blockIdx.x, threadIdx.x, nc);
 }
 
 }  // namespace mf

@@ -110,6 +110,27 @@ def test_acf_of_a_constant_series_is_nan(value):
         assert nc[0] == nc[2] == -1
 
 
+@pytest.mark.parametrize("t,nb,lag", [(2, 3, 0), (7, 2, 6), (8, 2, 3), (9, 2, 8), (257, 5, 256), (319, 2, 300),
+                                      (320, 3, 319), (321, 3, 320)])
+def test_acf_of_short_series(t, nb, lag):
+    """Series that one workgroup holds (up to 320 samples), around its runs of 8
+    products and 256 threads; NaN in one bin stays there."""
+    import torch
+    rng = np.random.default_rng(7 * t + nb)
+    x = -3.0 + rng.standard_normal((t, nb)).cumsum(axis=0)
+    x[t // 2, 1] = np.nan
+    c, nc = binding.acf(torch.from_numpy(x).cuda(), lag)
+    c, nc = c.cpu().numpy(), nc.cpu().numpy()
+    assert np.isnan(c[:, 1]).all() and nc[1] == -1
+    for b in set(range(nb)) - {1}:
+        ref = diagnostics.acf(x[:, b], lag)
+        low = np.flatnonzero(ref < 0.1)
+        # as above: rounding below t 2^-53 t/(t - n), another factor for the mean's offset
+        tol = 100 * t * 2.0 ** -53 * t / (t - np.arange(lag + 1))
+        assert np.all(np.abs(c[:, b] - ref) <= tol)
+        assert nc[b] == (low[0] if len(low) else -1)
+
+
 def test_graph_replays_record_too():
     w = workloads.small_workload(32, 8, precision="fp32", seed=71, rng_seed=72)
     pb = workloads.make_problem(w)
