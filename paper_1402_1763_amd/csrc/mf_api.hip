@@ -545,122 +545,117 @@ void launch_xmix(const mf::SweepArgs<R>& a, int nch, hipStream_t st) {
 }
 
 // xv, yv: split-path tile variants of the Gibbs x-pass and of the y-passes
-// (yv: units variant + 3 x radix order, launch_ysplit_v); the other x-pass
-// modes (mixing, Wiener) run x-tile variant 1.
+// (yv: units variant + 3 x radix order, launch_ysplit_v); the four-pass Wiener
+// iteration's x-pass runs x-tile variant 1, the mixing sweep's as launch_xmix
+// chooses.  False for a kernel that the size does not have on that path.
 template <typename R, int N>
-void launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool whole, int xv,
+bool launch_n(int id, const mf::SweepArgs<R>& a, int nch, hipStream_t st, bool whole, int xv,
               int yv) {
   using ZT = mf::ZTile<R, N>;
-  using XS = mf::XSTile<R, N, 1>;   // the modes other than Gibbs sampling
-  constexpr bool can_split = mf::split_x<N>();
-  const bool split = can_split && !whole;
   const dim3 zgrid(N / ZT::P, N / ZT::IXB, nch), zgrid1(N / ZT::P, N / ZT::IXB, 1);
   const size_t tables = 2 * a.nb * sizeof(R) + (a.nb + 1) * 4;
-  if constexpr (mf::has_planes<N>()) {
-    if (launch_plane_path<R, N>(id, a, nch, st)) return;
-  }
+  // every size on every path
   switch (id) {
-    case kZ:
-      hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZSweep>), zgrid, dim3(ZT::NT), 0, st, a);
-      break;
     case kZSet:
       hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZSetState>), zgrid1, dim3(ZT::NT), 0, st, a);
-      break;
+      return true;
     case kZGet:
       hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZGetState>), zgrid1, dim3(ZT::NT), 0, st, a);
-      break;
-    case kZDetK:
-      hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZDet>), zgrid, dim3(ZT::NT), 0, st, a);
-      break;
-    case kZAccK:
-      hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZAccum>), zgrid, dim3(ZT::NT), 0, st, a);
-      break;
-    case kYF:
-      if constexpr (can_split) {
-        if (split) {
-          launch_ysplit_v<R, N, false>(a, nch, st, yv);
-          break;
-        }
-      }
-      if constexpr (!mf::has_planes<N>()) {
-        using YT = mf::YTile<R, N>;
-        hipLaunchKernelGGL((mf::ypass_kernel<R, N, false>), dim3((N / 2 + 1) * N / YT::NPEN, 1, nch),
-                           dim3(YT::NT), 0, st, a);
-      }
-      break;
-    case kYI:
-      if constexpr (can_split) {
-        if (split) {
-          launch_ysplit_v<R, N, true>(a, nch, st, yv);
-          break;
-        }
-      }
-      if constexpr (!mf::has_planes<N>()) {
-        using YT = mf::YTile<R, N>;
-        hipLaunchKernelGGL((mf::ypass_kernel<R, N, true>),
-                           dim3((N / 2 + 1) * N / YT::NPEN + a.nb, 1, nch), dim3(YT::NT), 0, st, a);
-      }
-      break;
-    case kXDetK:
-      if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXDet, 1>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch),
-                           dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
-      break;
-    case kXMixK:
-      if constexpr (can_split) {
-        if (a.nb <= kMixBins8) launch_xmix<R, N, 0>(a, nch, st);
-        else launch_xmix<R, N, 1>(a, nch, st);
-      }
-      break;
-    case kXMixInvK:
-      if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xmixinv_kernel<R, N>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch), dim3(XS::NT),
-                           a.nb * sizeof(R) + (a.nb + 1) * 4, st, a);
-      break;
-    case kMixPkK:
-      hipLaunchKernelGGL((mf::mix_pk_kernel<R>), dim3(a.nb, nch), dim3(256), 0, st, a);
-      break;
-    case kXAdjK:
-      if constexpr (can_split)
-        hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXAdj, 1>), dim3(mf::plane_blocks(N, XS::WPP), 1, nch),
-                           dim3(XS::NT), mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
-      break;
-    case kX:
-      if constexpr (can_split) {
-        if (split) {
+      return true;
+    case kTable:
+      hipLaunchKernelGGL((mf::pk_table_kernel<R>), dim3((a.nb + 63) / 64, nch), dim3(64), 0, st, a);
+      return true;
+  }
+  if constexpr (mf::has_planes<N>()) {
+    if (launch_plane_path<R, N>(id, a, nch, st)) return true;
+  }
+  if constexpr (mf::split_x<N>()) {
+    if (!whole) {
+      using XS = mf::XSTile<R, N, 1>;
+      const dim3 xgrid(mf::plane_blocks(N, XS::WPP), 1, nch);
+      const size_t xlds = mf::hist_doubles(XS::NHIST, a.nb, 1) * sizeof(double) + tables;
+      switch (id) {
+        case kZ:
+          hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZSweep>), zgrid, dim3(ZT::NT), 0, st, a);
+          return true;
+        case kZDetK:
+          hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZDet>), zgrid, dim3(ZT::NT), 0, st, a);
+          return true;
+        case kZAccK:
+          hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZAccum>), zgrid, dim3(ZT::NT), 0, st, a);
+          return true;
+        case kYF: launch_ysplit_v<R, N, false>(a, nch, st, yv); return true;
+        case kYI: launch_ysplit_v<R, N, true>(a, nch, st, yv); return true;
+        case kX:
           if (xv == 1) launch_xsplit<R, N, 1>(a, nch, st);
           else if (xv == 2) launch_xsplit<R, N, 2>(a, nch, st);
           else launch_xsplit<R, N, 0>(a, nch, st);
-          break;
-        }
+          return true;
+        case kXDetK:
+          hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXDet, 1>), xgrid, dim3(XS::NT), xlds, st, a);
+          return true;
+        case kXAdjK:
+          hipLaunchKernelGGL((mf::xsplit_kernel<R, N, mf::kXAdj, 1>), xgrid, dim3(XS::NT), xlds, st, a);
+          return true;
+        case kXMixK:
+          if (a.nb <= kMixBins8) launch_xmix<R, N, 0>(a, nch, st);
+          else launch_xmix<R, N, 1>(a, nch, st);
+          return true;
+        case kMixPkK:
+          hipLaunchKernelGGL((mf::mix_pk_kernel<R>), dim3(a.nb, nch), dim3(256), 0, st, a);
+          return true;
+        case kXMixInvK:
+          hipLaunchKernelGGL((mf::xmixinv_kernel<R, N>), xgrid, dim3(XS::NT),
+                             a.nb * sizeof(R) + (a.nb + 1) * 4, st, a);
+          return true;
       }
-      if constexpr (!mf::has_planes<N>()) {
-        using XT = mf::XTile<R, N>;
-        hipLaunchKernelGGL((mf::xpass_kernel<R, N>), dim3(N / XT::P, N / 2 + 1, nch), dim3(XT::NT),
-                           mf::hist_doubles(XT::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
-      }
-      break;
-    case kTable:
-      hipLaunchKernelGGL((mf::pk_table_kernel<R>), dim3((a.nb + 63) / 64, nch), dim3(64), 0, st, a);
-      break;
+    }
   }
+  if constexpr (!mf::has_planes<N>()) {
+    if (whole) {
+      using YT = mf::YTile<R, N>;
+      using XT = mf::XTile<R, N>;
+      const int ywgs = (N / 2 + 1) * N / YT::NPEN;
+      switch (id) {
+        case kZ:
+          hipLaunchKernelGGL((mf::zpass_kernel<R, N, mf::kZSweep>), zgrid, dim3(ZT::NT), 0, st, a);
+          return true;
+        case kYF:
+          hipLaunchKernelGGL((mf::ypass_kernel<R, N, false>), dim3(ywgs, 1, nch), dim3(YT::NT), 0, st, a);
+          return true;
+        case kYI:
+          hipLaunchKernelGGL((mf::ypass_kernel<R, N, true>), dim3(ywgs + a.nb, 1, nch), dim3(YT::NT), 0, st, a);
+          return true;
+        case kX:
+          hipLaunchKernelGGL((mf::xpass_kernel<R, N>), dim3(N / XT::P, N / 2 + 1, nch), dim3(XT::NT),
+                             mf::hist_doubles(XT::NHIST, a.nb, 1) * sizeof(double) + tables, st, a);
+          return true;
+      }
+    }
+  }
+  return false;
 }
 
 template <typename R>
-void launch(int id, const mf::SweepArgs<R>& a, int n, int nch, hipStream_t st, bool whole = false,
-            int xv = 0, int yv = 0) {
+mf_status launch(int id, const mf::SweepArgs<R>& a, int n, int nch, hipStream_t st, bool whole = false,
+                 int xv = 0, int yv = 0) {
+  bool there = false;
   switch (n) {
-    case 8: launch_n<R, 8>(id, a, nch, st, whole, xv, yv); break;
-    case 16: launch_n<R, 16>(id, a, nch, st, whole, xv, yv); break;
-    case 32: launch_n<R, 32>(id, a, nch, st, whole, xv, yv); break;
-    case 48: launch_n<R, 48>(id, a, nch, st, whole, xv, yv); break;
-    case 64: launch_n<R, 64>(id, a, nch, st, whole, xv, yv); break;
-    case 80: launch_n<R, 80>(id, a, nch, st, whole, xv, yv); break;
-    case 96: launch_n<R, 96>(id, a, nch, st, whole, xv, yv); break;
-    case 128: launch_n<R, 128>(id, a, nch, st, whole, xv, yv); break;
-    case 256: launch_n<R, 256>(id, a, nch, st, whole, xv, yv); break;
-    case 512: launch_n<R, 512>(id, a, nch, st, whole, xv, yv); break;
+    case 8: there = launch_n<R, 8>(id, a, nch, st, whole, xv, yv); break;
+    case 16: there = launch_n<R, 16>(id, a, nch, st, whole, xv, yv); break;
+    case 32: there = launch_n<R, 32>(id, a, nch, st, whole, xv, yv); break;
+    case 48: there = launch_n<R, 48>(id, a, nch, st, whole, xv, yv); break;
+    case 64: there = launch_n<R, 64>(id, a, nch, st, whole, xv, yv); break;
+    case 80: there = launch_n<R, 80>(id, a, nch, st, whole, xv, yv); break;
+    case 96: there = launch_n<R, 96>(id, a, nch, st, whole, xv, yv); break;
+    case 128: there = launch_n<R, 128>(id, a, nch, st, whole, xv, yv); break;
+    case 256: there = launch_n<R, 256>(id, a, nch, st, whole, xv, yv); break;
+    case 512: there = launch_n<R, 512>(id, a, nch, st, whole, xv, yv); break;
   }
+  if (!there) return fail(MF_E_UNSUPPORTED_SIZE, "no kernel %d for N = %d on the %s path", id, n, whole ? "whole" : "split");
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(MF_E_DEVICE, "kernel %d launch failed: %s", id, hipGetErrorString(e));
+  return MF_OK;
 }
 
 // path < 0: the problem's Gibbs-sweep path and tile variants; a given path
@@ -679,18 +674,14 @@ mf_status launch_checked(mf_problem* p, int id, int staging_chain, hipStream_t s
     a.rev = rev;
     a.pk_mode = pk_mode;
     a.gam_sweeps = gam_sweeps;
-    launch<double>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
-  } else {
-    auto a = args_of<float>(p, path, xv);
-    a.staging_chain = staging_chain;
-    a.rev = rev;
-    a.pk_mode = pk_mode;
-    a.gam_sweeps = gam_sweeps;
-    launch<float>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
+    return launch<double>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
   }
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(MF_E_DEVICE, "kernel %d launch failed: %s", id, hipGetErrorString(e));
-  return MF_OK;
+  auto a = args_of<float>(p, path, xv);
+  a.staging_chain = staging_chain;
+  a.rev = rev;
+  a.pk_mode = pk_mode;
+  a.gam_sweeps = gam_sweeps;
+  return launch<float>(id, a, p->desc.n, nch, st, path == kPathWhole, xv, yv);
 }
 
 // The sweep index is Philox counter word 1, a 32-bit word: indices at or
@@ -1939,8 +1930,7 @@ mf_status wiener_iter(mf_problem* p, mf::SweepArgs<R> a, int nc, const mf::cx<R>
   const int split[4] = {kZDetK, kYF, adj ? kXAdjK : kXDetK, kYI};
   const int plane[2] = {kPlaneDet, adj ? kColumnAdj : kColumnDet};
   for (int k = 0; k < (planes ? 2 : 4); ++k) {
-    launch<R>(planes ? plane[k] : split[k], a, p->desc.n, nc, st);
-    const mf_status r = check_launch("Wiener iteration");
+    const mf_status r = launch<R>(planes ? plane[k] : split[k], a, p->desc.n, nc, st);
     if (r != MF_OK) return r;
   }
   return MF_OK;
@@ -1955,8 +1945,7 @@ mf_status wiener_finish(mf_problem* p, mf::SweepArgs<R> a, int nc, mf::cx<R>* sp
   a.spec_in = spec;
   a.spec = spec;
   a.pk_mode = open ? mf::kPkGrad : mf::kPkNone;
-  launch<R>(sums_only ? kPlanePk : kPlaneLast, a, p->desc.n, nc, st);
-  return check_launch("Wiener iteration's end");
+  return launch<R>(sums_only ? kPlanePk : kPlaneLast, a, p->desc.n, nc, st);
 }
 
 // y = x / R for chains c0 .. c0 + nc - 1 (y may be x).  A problem with a
@@ -2018,7 +2007,7 @@ mf_status wiener_forward(mf_problem* p, int c0, const double* d, const double* p
     auto ag = a;
     ag.spec_in = fwd;
     ag.staging_chain = c;
-    launch<R>(kZGet, ag, n, 1, st);
+    if ((r = launch<R>(kZGet, ag, n, 1, st)) != MF_OK) return r;
     with_n(n, [&](auto nn) {
       constexpr int N = decltype(nn)::value;
       hipLaunchKernelGGL((mf::wiener_chi2_kernel<R, N>), dim3(W.nblk), dim3(mf::kWienerThreads), 0,
@@ -2072,7 +2061,7 @@ mf_status wiener_backward(mf_problem* p, int c0, const double* d, char* g, const
         auto ag = a;
         ag.spec_in = fwd;
         ag.staging_chain = c;
-        launch<R>(kZGet, ag, n, 1, st);
+        if ((r = launch<R>(kZGet, ag, n, 1, st)) != MF_OK) return r;
         with_n(n, [&](auto nn) {
           constexpr int N = decltype(nn)::value;
           hipLaunchKernelGGL((mf::wiener_grad_direct_kernel<R, N>), dim3(W.nblk),
@@ -2098,7 +2087,7 @@ mf_status wiener_backward(mf_problem* p, int c0, const double* d, char* g, const
   if ((r = wiener_finish<R>(p, a, nc, adj, true, st)) != MF_OK) return r;
   a.spec_in = adj;
   a.acc = acc;
-  launch<R>(kZAccK, a, n, nc, st);   // adds r_0
+  if ((r = launch<R>(kZAccK, a, n, nc, st)) != MF_OK) return r;   // adds r_0
   for (int c = 0; c < nc; ++c) {
     with_n(n, [&](auto nn) {
       constexpr int N = decltype(nn)::value;

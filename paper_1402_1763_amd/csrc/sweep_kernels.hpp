@@ -144,10 +144,11 @@ struct ZTile {
   static constexpr int MIN_WAVES = (sizeof(R) == 8 && N == 256) ? 2 : 1;
 };
 
-// y-pass (whole-transform path): NPEN consecutive contiguous pencils of one
-// kz plane, q-fastest, padded LDS.
+// y-pass (whole-transform path of N = 256 and 512; smaller sides run planes):
+// NPEN consecutive contiguous pencils of one kz plane, q-fastest, padded LDS.
 template <typename R, int N>
 struct YTile {
+  static_assert(N >= 256, "smaller sides have no whole-transform y-pass");
   static constexpr int EPT = ept<N>();
   static constexpr int CAP = sizeof(R) == 4 ? 4096 : 2048;
   static constexpr int NPEN = divisor_below(N, CAP / N);
@@ -157,10 +158,11 @@ struct YTile {
   using TL = Tile<N, NPEN, NT, false, PSTR, PADS>;
 };
 
-// x-pass (whole-transform path): one kz plane, P consecutive iy columns,
-// pencil-fastest.
+// x-pass (whole-transform path of the same sides): one kz plane, P consecutive
+// iy columns, pencil-fastest.
 template <typename R, int N>
 struct XTile {
+  static_assert(N >= 256, "smaller sides have no whole-transform x-pass");
   static constexpr int EPT = ept<N>();
   static constexpr int CAP = 4096;
   static constexpr int P = divisor_below(N, CAP / N);
