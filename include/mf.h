@@ -150,7 +150,8 @@ mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
  * system-scope fence, so every kernel is timed on n_sweeps / MF_NUM_KERNELS
  * sweeps (NaN for a kernel never timed: n_sweeps < MF_NUM_KERNELS).  Where
  * mf_gibbs_sweep joins kernels (mf_set_tuning, the two-pass sweep), this call
- * runs their parts one by one, with the same results to the last bit. */
+ * runs their parts one by one, with the same results to the last bit; the parts
+ * take longer than their share of the joined launches. */
 mf_status mf_gibbs_sweep_timed(mf_problem* p, int32_t n_sweeps, void* stream,
                                double* kernel_ms, int32_t n_kernels);
 
@@ -292,12 +293,18 @@ mf_status mf_autotune(mf_problem* p, int32_t trials, void* stream, double* ms, m
 /* Algorithmic HBM bytes of one sweep, per kernel (bytes[MF_NUM_KERNELS], in
  * sweep order), summed over the problem's chains.  Each pass reads and
  * writes the half-complex field once, 2 (N/2 + 1) N^2 reals each way.  On
- * top of that (on the two-pass sweep the y-passes move nothing of their own):
+ * the two-pass sweep the y-passes are part of the z-pass and move nothing of
+ * their own: the figures are those of a further sweep of a run, and
+ * mf_gibbs_sweep_timed's durations of its parts launched one by one, each of
+ * which reads and writes the field, are not to be divided into them.  On top of
+ * that:
  *  - the z-pass reads the two messenger coefficients of every voxel in the
  *    chunks of its tiles that hold an observed voxel (a chunk is one element
  *    of every lane of a tile; chunks with none skip the read);
  *  - the x-pass writes one FP64 shell partial per bin and workgroup;
- *  - the inverse y-pass reads those partials and updates P and its table.
+ *  - the inverse y-pass reads those partials and updates P and its table;
+ *  - on the two-pass sweep of at most 128 FP64 planes, the x-pass writes and the
+ *    next z-pass reads the messenger's normals, one real per voxel.
  * These are the per-unit figures behind the roofline of each kernel. */
 mf_status mf_sweep_bytes(const mf_problem* p, size_t* bytes);
 

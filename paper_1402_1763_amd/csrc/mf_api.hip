@@ -1516,12 +1516,13 @@ mf_status mf_sweep_bytes(const mf_problem* p, size_t* bytes) {
   const size_t spec = (n / 2 + 1) * n * n * 2 * rs;
   const size_t part = static_cast<size_t>(p->n_wg(p->sweep_path(), p->xvar)) * nb * 8;
   const size_t y = p->planes() ? 0 : 2 * spec;   // the plane kernel's y transforms move nothing
+  const size_t nrm = p->planes() && draws_ahead(p->desc) ? m * rs : 0;   // normals drawn ahead
   for (int k = 0; k < MF_NUM_KERNELS; ++k) bytes[k] = 0;
   for (int c = 0; c < p->desc.n_chains; ++c) {
     const size_t coef = 2 * m * rs * static_cast<size_t>(p->obs_chunks[c]) / (p->sh.ztiles * p->sh.zept);
-    bytes[0] += 2 * spec + coef;
+    bytes[0] += 2 * spec + coef + nrm;
     bytes[1] += y;
-    bytes[2] += 2 * spec + part;
+    bytes[2] += 2 * spec + part + nrm;
     bytes[3] += y + part + nb * (16 + 2 * rs);
   }
   return MF_OK;

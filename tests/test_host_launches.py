@@ -291,3 +291,28 @@ def test_every_chain_starts_on_the_same_xcd(run):
                 if kernel.startswith(("ysplit", "xsplit", "xmixinv", "plane")):
                     assert int(grid.split()[0]) % 8 == 0, line
     """)
+
+
+def test_sweep_bytes_count_the_normals_drawn_ahead(run):
+    """FP64 problems of at most 128 planes write and read one real per voxel more
+    on the two-pass sweep, and only there."""
+    run("""
+        def nbytes(h):
+            out = (ctypes.c_size_t * binding.MF_NUM_KERNELS)()
+            assert lib.mf_sweep_bytes(ctypes.c_void_p(h), out) == 0
+            return list(out)
+        for n, precision, chains in ((32, "fp64", 1), (32, "fp64", 4), (32, "fp64", 5), (64, "fp32", 1), (64, "fp64", 2)):
+            h = problem(n, precision, chains)
+            rs, m = (8 if precision == "fp64" else 4), n ** 3
+            spec = (n // 2 + 1) * n * n * 2 * rs
+            two = nbytes(h)
+            assert lib.mf_set_x_path(ctypes.c_void_p(h), 0) == 0
+            four = nbytes(h)
+            ahead = chains * m * rs if precision == "fp64" and n * chains <= 128 else 0
+            assert two[0] - four[0] == ahead
+            assert two[1] == 0 and four[1] == 2 * spec * chains
+            # every launch that the bytes describe is there: a column kernel that draws ahead
+            assert lib.mf_set_x_path(ctypes.c_void_p(h), 1) == 0
+            log(); sweep(h, 2)
+            assert any("column_kernel" in k and k.endswith("true>") for k in names(log())) == (ahead > 0)
+    """)
