@@ -138,8 +138,9 @@ mf_status mf_init_problem(const mf_chain_desc* desc, const double* const* data,
  * The sweeps may be captured by the caller: replays draw by the sweep index on
  * the device, and mf_set_chain_state brings the host's count in line.
  * Where a launch of the two-pass sweep (mf_set_x_path) fails, the next call
- * that uses the field first completes the sweep that was cut short and ends the
- * run, on its own stream (MF_E_STATE while that is being captured).
+ * that uses the problem's device state first completes the sweep that was cut
+ * short and ends the run, on its own stream (MF_E_STATE while that is being
+ * captured).
  * Errors: MF_E_INVALID_ARG (also that bound), MF_E_STATE, MF_E_DEVICE. */
 mf_status mf_gibbs_sweep(mf_problem* p, int32_t n_sweeps, void* stream);
 

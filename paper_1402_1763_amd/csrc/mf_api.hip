@@ -2131,6 +2131,7 @@ mf_status mf_wiener_forward(mf_problem* p, int32_t chain, const double* d, const
   if (!d || !pk || !chi2) return fail(MF_E_INVALID_ARG, "d, pk and chi2 must be device pointers");
   p->wiener = WienerRun{};
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  if ((r = settle(p, hs)) != MF_OK) return r;   // the P draw's partials, before they are scratch
   char* g = static_cast<char*>(workspace);
   r = p->fp64() ? wiener_forward<double>(p, c0, d, pk, n_iter, ckpt_every, g, W, chi2, s_out, hs)
                 : wiener_forward<float>(p, c0, d, pk, n_iter, ckpt_every, g, W, chi2, s_out, hs);
@@ -2149,6 +2150,7 @@ mf_status mf_wiener_backward(mf_problem* p, int32_t chain, const double* d, void
   if (r != MF_OK) return r;
   if (!d || !grad_d || !grad_pk) return fail(MF_E_INVALID_ARG, "d, grad_d and grad_pk must be device pointers");
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  if ((r = settle(p, hs)) != MF_OK) return r;
   char* g = static_cast<char*>(workspace);
   return p->fp64() ? wiener_backward<double>(p, c0, d, g, W, grad_d, grad_pk, hs)
                    : wiener_backward<float>(p, c0, d, g, W, grad_d, grad_pk, hs);
@@ -2296,6 +2298,7 @@ mf_status mf_wiener_logdet_trace(mf_problem* p, int32_t chain, const double* pk,
   if (ws_bytes < L.total)
     return fail(MF_E_WORKSPACE, "log-determinant workspace too small: %zu < %zu", ws_bytes, L.total);
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  if ((r = settle(p, hs)) != MF_OK) return r;
   char* g = static_cast<char*>(workspace);
   return p->fp64() ? logdet_run<double>(p, c0, pk, n_iter, n_probes, probe0, g, L, trace_out, hs)
                    : logdet_run<float>(p, c0, pk, n_iter, n_probes, probe0, g, L, trace_out, hs);
@@ -2362,6 +2365,7 @@ mf_status mf_wiener_logdet_trace_noalloc(mf_problem* p, int32_t chain, const dou
   void* g = nullptr;
   if ((r = scratch_address(&g)) != MF_OK) return r;
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  if ((r = settle(p, hs)) != MF_OK) return r;
   char* gc = static_cast<char*>(g);
   return p->fp64() ? logdet_run<double>(p, c0, pk, n_iter, n_probes, probe0, gc, L, trace_out, hs)
                    : logdet_run<float>(p, c0, pk, n_iter, n_probes, probe0, gc, L, trace_out, hs);
@@ -2427,6 +2431,8 @@ mf_status mf_set_diagnostics(mf_problem* p, uint64_t start, int32_t thin, double
     if (q && reinterpret_cast<uintptr_t>(q) % 8 != 0)
       return fail(MF_E_INVALID_ARG, "diagnostic buffers must be 8-byte aligned");
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  const mf_status whole = settle(p, hs);   // what is owed records with the settings it began with
+  if (whole != MF_OK) return whole;
   if (moments) {
     const size_t m = static_cast<size_t>(p->desc.n) * p->desc.n * p->desc.n;
     hipLaunchKernelGGL((mf::fill_zero_kernel<double>), dim3(1024), dim3(256), 0, hs, moments,

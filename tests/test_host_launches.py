@@ -122,6 +122,41 @@ def test_every_call_on_the_field_completes_a_run_first(run):
     """)
 
 
+def test_calls_on_the_scratch_and_the_records_complete_a_run_first(run):
+    """The Wiener filter and the log-determinant use the P draw's partials as
+    scratch, and new diagnostics would take an old sweep's records."""
+    run("""
+        end = "plane_kernel<float, 64, true, -1, false"
+        def broken():
+            h = problem(64)
+            stub.stub_fail_launch(2)
+            assert sweep(h, 3) == binding.MF_E_DEVICE
+            log()
+            return h
+        def device(doubles):
+            problem.keep.append(np.zeros(doubles + 64))
+            return (problem.keep[-1].ctypes.data + 255) // 256 * 256
+        field, bins = device(64 ** 3), device(8)
+        h = broken()
+        size = binding.mf_wiener_workspace_bytes(h, 0, 2, 1)
+        ws = device(size // 8 + 1)
+        binding.mf_wiener_forward(h, 0, field, bins, 2, 1, ws, size, bins, None, 0); first = log()[0]
+        assert first.startswith(end), first
+        stub.stub_fail_launch(2); assert sweep(h, 3) == binding.MF_E_DEVICE; log()
+        binding.mf_wiener_backward(h, 0, field, ws, size, field, bins, 0); assert log()[0].startswith(end)
+        h = broken()
+        out = ctypes.c_size_t(0)
+        assert lib.mf_wiener_logdet_workspace_bytes(ctypes.c_void_p(h), 0, ctypes.byref(out)) == 0
+        ws = device(out.value // 8 + 1)
+        assert lib.mf_wiener_logdet_trace(ctypes.c_void_p(h), 0, ctypes.c_void_p(bins), 2, 1, 0, ctypes.c_void_p(ws),
+                                          out.value, ctypes.c_void_p(bins), None) == 0
+        assert log()[0].startswith(end)
+        h = broken()
+        assert lib.mf_set_diagnostics(ctypes.c_void_p(h), ctypes.c_uint64(0), 1, ctypes.c_void_p(device(64)), 4, None, None) == 0
+        assert log()[0].startswith(end)
+    """)
+
+
 def test_a_graph_launch_that_fails_counts_and_completes_its_sweeps(run):
     """The failing step of a launch of 10 sweeps: the first sweep's launches,
     replays of four, the sweep left over or the end."""
