@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libmfgibbs.so")
 SOURCES = [os.path.join(HERE, "csrc", "mf_api.hip")]
-HEADERS = [os.path.join(HERE, "csrc", f) for f in ("fft.hpp", "philox.hpp", "sweep_kernels.hpp")]
+HEADERS = [os.path.join(HERE, "csrc", f) for f in sorted(os.listdir(os.path.join(HERE, "csrc"))) if f.endswith(".hpp")]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950",

@@ -30,7 +30,7 @@
 // product fused across statements depends on what the optimizer sees around it,
 // and the kernels that compute one thing in several instantiations (the plane
 // kernel's joined and separate launches, its two workgroup sizes) have to agree
-// to the last bit.
+// to the last bit.  It holds for every kernel that includes this file.
 #pragma clang fp contract(on)
 
 namespace mf {

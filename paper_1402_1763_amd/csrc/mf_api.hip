@@ -166,9 +166,11 @@ struct Layout {
 
 // The column kernel computes the next sweep's messenger normals where the plane
 // kernel occupies at most half of the 256 CUs, in FP64, whose draws take the
-// most instructions.  us per sweep without : with: 16^3 13.5 : 11.8, 32^3 13.9 :
-// 12.6, 64^3 21.1 : 19.0, 80^3 33.2 : 29.5, 128^3 71.1 : 63.6; in FP32 it would
-// cost as much as it gives (64^3 13.0 : 13.0, 96^3 22.3 : 23.2, 128^3 30.4 : 31.0).
+// most instructions.  us per sweep without : with, one chain: 8^3 15.2 : 13.7, 16^3
+// 13.8 : 12.5, 32^3 14.1 : 12.8, 64^3 20.8 : 18.6, 80^3 32.5 : 28.9, 96^3 47.8 :
+// 43.0, 128^3 70.3 : 64.1; several: 16 of 8^3 16.3 : 14.8, 8 of 16^3 14.0 : 12.6, 4
+// of 32^3 15.0 : 13.8, 2 of 64^3 24.1 : 23.5; in FP32 it would cost as much as it
+// gives (64^3 13.0 : 13.0, 96^3 22.3 : 23.2, 128^3 30.4 : 31.0).
 bool draws_ahead(const mf_chain_desc& d) {
   return d.precision == MF_PREC_FP64 && d.n <= kMaxPlaneN && d.n * d.n_chains <= 128;
 }
@@ -332,12 +334,15 @@ struct mf_problem {
   enum Owed { kNothing, kOwesColumn, kOwesEnd };
   Owed owed = kNothing;
   // Where the plane path is the faster one, by the problem alone (not by the
-  // chains of a call), us per sweep against the split path: one FP64 chain of
-  // 16^3 11.8 : 39.8, 32^3 12.5 : 39.8, 80^3 28.6 : 53.7, 128^3 63.6 : 73.5; one
-  // FP32 chain of 64^3 12.8 : 25.4, 96^3 21.4 : 30.1, 128^3 28.2 : 41.8; 32 FP32
-  // chains of 64^3 46.8 : 67.8, 8 of 96^3 60.4 : 69.3, 8 of 128^3 100 : 119.  FP64
-  // planes of 96^3 and 128^3 fill a CU's LDS and registers by themselves, so
-  // queues of them do not overlap: 8 chains of 96^3 157 : 152, 4 of 128^3 170 : 165.
+  // chains of a call), us per sweep planes : split path with its default tiles.
+  // One chain: FP64 32^3 12.9 : 38.7, 80^3 29.2 : 51.4, 96^3 43.1 : 54.4, 128^3
+  // 64.3 : 68.9; FP32 64^3 13.3 : 25.4, 96^3 21.5 : 29.8, 128^3 28.7 : 36.1.
+  // Queues: 32 FP32 chains of 64^3 47.2 : 69.7, 8 of 80^3 39.7 : 56.2, of 96^3 61.1
+  // : 65.8, of 128^3 98.2 : 119; FP64, 32 of 64^3 135 : 182, 8 of 80^3 94 : 123.
+  // FP64 planes of 96^3 and 128^3 fill a CU's LDS and registers by themselves (and
+  // spill 14 to 59 of the latter), so queues of them do not overlap: 2 chains of
+  // 96^3 58.1 : 66.7, 3 of them 92.0 : 74.4, 4 98.5 : 96.5; 2 of 128^3 91.0 : 93.9,
+  // 3 142 : 135, 4 164 : 164.
   bool prefers_planes() const {
     return desc.n <= kMaxPlaneN && !(fp64() && desc.n >= 96 && desc.n * desc.n_chains > 256);
   }

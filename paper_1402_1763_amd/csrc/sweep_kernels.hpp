@@ -705,7 +705,7 @@ __host__ __device__ constexpr bool split_x() { return N >= 32 && N <= 256; }
 // what an XCD wrote last it reads first, still in its L2.  A performance
 // matter only: any other placement computes the same.
 // 256^3 FP32: x-pass 30.0 -> 28.4 us, inverse y-pass 23.9 -> 22.5 us, a sweep
-// 115.3 -> 112.0 us; planes by XCD without the reversal 114.5, the reversal
+// 115.3 -> 112.5 us; planes by XCD without the reversal 114.5, the reversal
 // with planes spread over the XCDs 114.9.  The plane kz = N/2, the one over a
 // multiple of 8, is spread over the XCDs at the end (on one XCD it costs 6% at
 // 96^3).
@@ -1140,8 +1140,8 @@ __device__ __forceinline__ void draw_epilogue(const SweepArgs<R>& a, int c, doub
 // 255 bins (neighbouring lanes hold neighbouring iy, whose bins are mostly
 // equal, so more copies mean fewer lanes adding to one address per
 // instruction: the 256^3 x-pass takes 32.0 us against 33.6 us with 2
-// copies); 1 is the same tile with 2 copies, for any bin count and for the
-// mixing sweep and the Wiener iteration; 2 splits every column over a pair
+// copies); 1 is the same tile with 2 copies, for any bin count, for mixing sweeps
+// of more than 96 bins and for the four-pass Wiener iteration; 2 splits every column over a pair
 // of neighbouring lanes (LANES = 2), each holding 8 of its 16 rows, with 8
 // copies: twice the waves, each with half the work, for a grid that
 // otherwise gives each SIMD few rounds of waves (below).  The autotuner
@@ -1163,7 +1163,8 @@ struct XSTile {
   static constexpr int MAX_BINS = HG == 8 ? 255 : 1024;   // 8 copies: 64 KiB of LDS at most
   static_assert(N % P == 0 && NA % K1 == 0 && NT <= 256, "x-pass tile must cover the plane");
   // FP32 at N = 256 would take 98 VGPRs (4 waves per SIMD); held to 96 (5
-  // waves, no spill) the pass runs 33.2 us instead of 35.5 us.
+  // waves) the pass runs 33.2 us instead of 35.5 us.  The branch of the two
+  // Hermitian planes then spills 4 registers; that of the 127 others none.
   static constexpr int MIN_WAVES = (V < 2 && sizeof(R) == 4 && N == 256) ? 5 : 1;
 };
 

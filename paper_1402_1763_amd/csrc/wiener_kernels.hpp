@@ -250,7 +250,7 @@ moments_kernel(const double* mom, double count, double* mean_out, double* var_ou
 // whole series in tiles of kAcfRows rows, the next tile's loads in flight
 // during the products of this one.  The 64 threads of a bin each hold kAcfRun
 // consecutive rows and the kAcfRun + kAcfLags - 1 later rows their lags need:
-// 39 LDS reads for 128 products.  An LDS run of 16 is padded to 17, which puts
+// 39 LDS reads for 128 products (254 VGPRs and 8 spilled outside the products).  An LDS run of 16 is padded to 17, which puts
 // the 32 threads of a bin on different banks.  All sums run in a fixed order.
 // 8000 samples of 32 bins, 400 lags: 48.2 us a call; one workgroup per bin and
 // whole lags per thread, read from memory, took 2,320 us.  The series is walked
