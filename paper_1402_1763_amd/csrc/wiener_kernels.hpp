@@ -250,9 +250,9 @@ moments_kernel(const double* mom, double count, double* mean_out, double* var_ou
 // whole series in tiles of kAcfRows rows, the next tile's loads in flight
 // during the products of this one.  The 64 threads of a bin each hold kAcfRun
 // consecutive rows and the kAcfRun + kAcfLags - 1 later rows their lags need:
-// 39 LDS reads for 128 products (254 VGPRs and 8 spilled outside the products).  An LDS run of 16 is padded to 17, which puts
+// 39 LDS reads for 128 products (254 VGPRs and 14 spilled outside the products).  An LDS run of 16 is padded to 17, which puts
 // the 32 threads of a bin on different banks.  All sums run in a fixed order.
-// 8000 samples of 32 bins, 400 lags: 48.2 us a call; one workgroup per bin and
+// 8000 samples of 32 bins, 400 lags: 46.5 us a call; one workgroup per bin and
 // whole lags per thread, read from memory, took 2,320 us.  The series is walked
 // tile by tile, and each tile costs one load latency: 512 rows by 256 threads
 // take 55.8 us, 256 rows 99 us, and loads under a condition 115 us.
@@ -284,12 +284,21 @@ acf_kernel(const double* trace, int t, int nb, int max_lag, int64_t items, doubl
     // constant series is that sample exactly: 64 strided sums, added in order
     const double x0 = col[0];
     double sum = 0.0;
-    for (int64_t i0 = 0; i0 < t; i0 += 32 * ROWS_PER_LOAD) {
+    constexpr int MEAN_ROWS = 32 * ROWS_PER_LOAD;
+    int64_t im = 0;
+    for (; im + MEAN_ROWS <= t; im += MEAN_ROWS) {
       double x[32];
 #pragma unroll
-      for (int k = 0; k < 32; ++k) x[k] = row_at(i0 + lrow + k * ROWS_PER_LOAD);
+      for (int k = 0; k < 32; ++k) x[k] = col[static_cast<size_t>(im + lrow + k * ROWS_PER_LOAD) * nb];
 #pragma unroll
-      for (int k = 0; k < 32; ++k) sum += i0 + lrow + k * ROWS_PER_LOAD < t ? x[k] - x0 : 0.0;
+      for (int k = 0; k < 32; ++k) sum += x[k] - x0;
+    }
+    if (im < t) {
+      double x[32];
+#pragma unroll
+      for (int k = 0; k < 32; ++k) x[k] = row_at(im + lrow + k * ROWS_PER_LOAD);
+#pragma unroll
+      for (int k = 0; k < 32; ++k) sum += im + lrow + k * ROWS_PER_LOAD < t ? x[k] - x0 : 0.0;
     }
     red[tid] = sum;
     __syncthreads();
