@@ -118,8 +118,8 @@ mf_status mf_workspace_bytes(const mf_chain_desc* desc, size_t* bytes);
  * Per chain, tau is the smallest observed N_i / R_i^2 (the bound of Sec. 2)
  * unless desc->tau > 0, which must not exceed it (MF_E_TAU).  The messenger
  * conditional of Sec. 3.1 is folded into per-voxel coefficients
- * alpha = 1 - tau R^2 / N and beta = tau R d / N, formed in FP64 on the host
- * and uploaded; the sweep itself does not depend on R otherwise.  Enqueues on
+ * alpha = 1 - tau R^2 / N and beta = tau R d / N, formed in FP64 on the device;
+ * the sweep itself does not depend on R otherwise.  Enqueues on
  * `stream` and synchronises it.
  * Errors: MF_E_INVALID_ARG (also a response given or missing against
  * desc->has_response), MF_E_UNSUPPORTED_SIZE, MF_E_TAU, MF_E_NONFINITE,

@@ -550,8 +550,8 @@ class Sampler:
 
 
 class SweepGraph:
-    """One HIP graph that sweeps several samplers (independent chains of any
-    sizes) once per replay."""
+    """HIP graphs that sweep several samplers (independent chains of any sizes)
+    as concurrent branches."""
 
     def __init__(self, samplers: Sequence["Sampler"]):
         import torch
