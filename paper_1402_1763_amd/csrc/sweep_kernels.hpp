@@ -723,6 +723,16 @@ __device__ __forceinline__ bool plane_block(int lin, int per_plane, bool rev, in
   return w < per_plane;
 }
 
+// Chain of a workgroup: every other pass (the y-passes; with the mixing sweep's
+// rescaling pass between them, that one in place of the last) takes the chains of
+// a launch from the last one on, whose planes the pass before wrote last.  us per
+// sweep, first chain first : by turns, 8 FP64 chains of 96^3 156.2 : 151.3 (four
+// passes without the XCD mapping 152.1), 4 of 128^3 165.0 : 161.8, 8 of 96^3 with
+// the mixing move 179.9 : 177.5; 4 FP32 chains of 128^3 with it 85.2 : 85.3.
+__device__ __forceinline__ int pass_chain(bool backwards) {
+  return static_cast<int>(backwards ? gridDim.z - 1 - blockIdx.z : blockIdx.z);
+}
+
 // Workgroups of such a pass over one chain: up to a multiple of 8 (plane_block is
 // false for the rest), so that the planes of every chain keep their XCDs.  us per
 // sweep, odd workgroups : in eights, 3 FP64 chains of 96^3 79.6 : 74.5, 4 of them
@@ -771,9 +781,10 @@ ysplit_kernel(SweepArgs<R> a) {
   __shared__ cx<R> tw[N];
   static_assert(G * NA * T::PSTR * sizeof(cx<R>) >= NT * sizeof(double), "reduction space");
   int blk = blockIdx.x;
+  const int c = pass_chain(!(INV && a.rev));
   if (INV) {
     if (blk < a.nb) {
-      pk_draw_block<R, NT>(a, blk, blockIdx.z, reinterpret_cast<double*>(lds), a.ctr[1]);
+      pk_draw_block<R, NT>(a, blk, c, reinterpret_cast<double*>(lds), a.ctr[1]);
       return;
     }
     blk -= pk_blocks(a.nb);
@@ -787,7 +798,7 @@ ysplit_kernel(SweepArgs<R> a) {
   q0 *= G;
   const int ug = tid / TPU, ut = tid % TPU;   // this thread's unit and rank in it (stage A)
   const int q = q0 + ug;
-  cx<R>* plane = a.spec + static_cast<size_t>(blockIdx.z) * a.spec_stride +
+  cx<R>* plane = a.spec + static_cast<size_t>(c) * a.spec_stride +
                  static_cast<size_t>(kz) * N * N;
   load_twiddles(tw, a.tw, N, NT);
   cx<R> v[EPT];
@@ -1292,7 +1303,7 @@ xmixinv_kernel(SweepArgs<R> a) {
   const int tid = threadIdx.x, nb = a.nb;
   int kz = 0, wp = 0;
   if (!plane_block<N>(blockIdx.x, T::WPP, false, kz, wp)) return;
-  const int iy0 = (wp / T::KB) * P, c = blockIdx.z;
+  const int iy0 = (wp / T::KB) * P, c = pass_chain(true);
   R* rat = reinterpret_cast<R*>(dyn);
   int32_t* qthr = reinterpret_cast<int32_t*>(rat + nb);
   for (int i = tid; i < nb; i += NT) rat[i] = static_cast<R>(a.ratio[static_cast<size_t>(c) * nb + i]);
